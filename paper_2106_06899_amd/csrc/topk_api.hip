@@ -138,7 +138,7 @@ int64_t caph_for(const Problem& pb, int path) { return path == PATH_FILTER && pb
 
 void choose_path(const Problem& pb, Plan* pl) {
   pl->path = PATH_TILE;
-  pl->scan = {MODE_ALL, 16, 8, 2, 0, 0};
+  pl->scan = {MODE_SAMPLE, 16, 12, 2, 0, 0};
   if (pb.tile_only) {
     if (filter_ok(pb)) pl->path = PATH_FILTER;
     return;
@@ -155,10 +155,8 @@ void choose_path(const Problem& pb, Plan* pl) {
     if (filter_ok(pb)) pl->path = PATH_FILTER;
     return;
   }
-  if (pb.Lk <= 2 * FUSED_CAPH) {  // every key fits the candidate buffers
+  if (pb.Lk <= ROWS_MAX_LK) {  // runs as short rows (rows_ok); topk_attn_path reports it as path 1
     pl->path = PATH_FUSED;
-    pl->scan = sample_rule(pb.k, pb.d, groups);  // its kernel instantiation; no sample is taken
-    pl->scan.mode = MODE_ALL;
     return;
   }
   // Threshold mode, see sample_rule: needs at least 2R sampled 16-key blocks in the
@@ -251,7 +249,7 @@ int split_rows(const Problem& pb, Problem* parts) {
   parts[0] = pb;
   Plan pl;
   choose_path(pb, &pl);
-  if (!pb.causal || pl.path != PATH_FUSED || pl.scan.mode != MODE_SAMPLE) return 1;
+  if (rows_ok(pb) || !pb.causal || pl.path != PATH_FUSED) return 1;
   const int64_t T = sample_rows_needed(pl.scan);
   if (T <= pb.q0) return 1;
   parts[0].q1 = pb.q1 < T ? pb.q1 : T;
@@ -263,10 +261,29 @@ int split_rows(const Problem& pb, Problem* parts) {
 }
 
 // ---------------------------------------------------------------- execution
+// Short rows: one kernel, no workspace, no fallback rows.
+int run_rows(const Problem& pb, hipStream_t st, bool report) {
+  if (report) g_fallback_rows = -1;
+  hipError_t e;
+  {
+    StageTimer t(st, ST_SCORE);
+    e = launch_rows(pb, st);
+  }
+  bool wait = report;  // debug calls wait for their stream
+#ifdef TOPK_CHECK_INDICES
+  wait = true;  // as do checked builds, see run()
+#endif
+  if (e == hipSuccess && wait) e = hipStreamSynchronize(st);
+  if (e != hipSuccess) return fail(TOPK_E_HIP, "kernel launch failed: %s", hipGetErrorString(e));
+  if (report) g_fallback_rows = 0;
+  return TOPK_OK;
+}
+
 // report: read back the rows a fallback selected (waits for the stream; debug calls)
 // fixed_ws / fixed_bytes: a workspace the call must run in (no allocation, no
 // registered workspace); the plan then fits its passes into fixed_bytes.
 int run(Problem whole, hipStream_t st, bool report, void* fixed_ws = nullptr, size_t fixed_bytes = 0) {
+  if (rows_ok(whole)) return run_rows(whole, st, report);
   Problem parts[2];
   Plan plans[2];
   const int np = split_rows(whole, parts);
@@ -446,6 +463,7 @@ int debug_ptrs(int32_t* idx_out, float* score_out) {
 }
 
 size_t workspace_for(const Problem& whole) {
+  if (rows_ok(whole)) return ALIGN;  // the single kernel uses none; 0 would mean invalid arguments
   Problem parts[2];
   const int np = split_rows(whole, parts);
   const size_t budget = g_budget.load(std::memory_order_relaxed);

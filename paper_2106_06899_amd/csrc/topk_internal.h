@@ -10,10 +10,10 @@ namespace topk {
 enum Act { ACT_SOFTMAX = 0, ACT_RELU = 1 };
 enum ElemType { T_F32 = 0, T_BF16 = 1 };
 
-// Sampling modes of the fused scan: ALL keeps every valid score as a candidate;
-// SAMPLE first estimates a per-query threshold from a strided subset of key tiles.
-// THRESH takes each query's threshold from the filtered path's sample (PassBufs::thr).
-enum ScanMode { MODE_ALL = 0, MODE_SAMPLE = 1, MODE_THRESH = 2 };
+// Sampling modes of the fused scan: SAMPLE first estimates a per-query threshold from a
+// strided subset of key tiles; THRESH takes each query's threshold from the filtered
+// path's sample (PassBufs::thr).
+enum ScanMode { MODE_SAMPLE = 1, MODE_THRESH = 2 };
 
 constexpr int REDO_CAP = 1024;          // redo rows recomputed by the wide fallback kernels
 constexpr int REDO_SPLIT = 512;         // keys per work item of the wide fallback
@@ -86,6 +86,17 @@ struct ScanCfg {
   int union_rank;     // SAMPLE: J > 0: the threshold is the J-th largest of both half-waves'
                       // lists together (13 or 20); 0: the smaller of their R-th
 };
+
+// Short rows (topk_rows.hip): calls whose rows have at most ROWS_MAX_LK keys and keep at
+// most ROWS_MAX_K of them run as one kernel that needs no workspace, whatever the chunk
+// size. The feature sizes are those the kernel is built for. Longer rows would not fit
+// a workgroup's LDS at 32 rows each; more than 256 kept keys would need more sort scratch.
+constexpr int ROWS_MAX_LK = 1024, ROWS_MAX_K = 256;
+inline bool rows_ok(const Problem& pb) {
+  return !pb.tile_only && pb.Lk <= ROWS_MAX_LK && pb.k <= ROWS_MAX_K &&
+         (pb.d == 32 || pb.d == 64 || pb.d == 96 || pb.d == 128);
+}
+hipError_t launch_rows(const Problem& pb, hipStream_t st);
 
 hipError_t launch_init(const PassBufs& b, hipStream_t st);
 hipError_t launch_tile_scores(const Problem& pb, const Pass& ps, const PassBufs& b, hipStream_t st);

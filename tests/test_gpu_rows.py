@@ -1,0 +1,91 @@
+"""GPU tests of the short-row kernel (rows of at most 1024 keys, k <= 256, d = 32, 64, 96
+or 128): against the fp64 oracle at the edges of its key groups, row tiles and outputs,
+ties at the k-th score, and value rows that are not finite."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2106_06899_amd as tk
+from paper_2106_06899_amd import workloads as wl
+from tests import parity
+
+pytestmark = pytest.mark.gpu
+
+# (B, H, Lq, Lk, d, k, causal): key counts around the 64-key waves and the 256- and
+# 512-key kernel sizes; row counts around the 16- and 32-row tiles; 512 heads fill enough
+# workgroups for 32-row tiles; k around the sizes of the cache outputs' sort
+CASES = [
+    (1, 1, 1, 1, 32, 1, False), (1, 2, 17, 63, 64, 64 - 1, False), (1, 1, 33, 65, 96, 64, False),
+    (1, 1, 15, 255, 128, 65, True), (2, 1, 16, 256, 64, 128, False), (1, 1, 40, 257, 32, 129, False),
+    (1, 2, 530, 511, 64, 20, True), (1, 1, 31, 513, 96, 256, False), (1, 1, 20, 1000, 128, 200, False),
+    (1, 1, 1100, 1024, 64, 100, True), (16, 32, 33, 130, 64, 40, False), (32, 16, 31, 520, 128, 128, False),
+    (16, 32, 20, 300, 96, 3, True), (16, 32, 5, 1024, 32, 200, False),
+]
+
+
+@pytest.mark.parametrize("dtype", [wl.BF16, wl.F32])
+@pytest.mark.parametrize("case", CASES)
+def test_short_rows(case, dtype):
+    B, H, Lq, Lk, d, k, causal = case
+    w = wl.WORKLOADS["c2"].scaled(B=B, H=H, Lq=Lq, Lk=Lk, d=d, k=k, causal=causal, dtype=dtype, chunk=7)
+    print("[case]", w, flush=True)
+    x = wl.make_inputs(w)
+    out, idx, sc = parity.run_attn(w, x)
+    rows = parity.sample_attn_rows(w, min(400, B * H * Lq), seed=5)
+    parity.check_attn(w, x, out, idx, rows=rows)
+    # every row: k_eff distinct valid keys, and the same bits without the cache outputs
+    g = idx.cpu().numpy().reshape(B * H, Lq, k)
+    k_eff = np.minimum(k, np.arange(Lq) + 1) if causal else np.full(Lq, k)
+    assert np.array_equal((g >= 0).sum(-1), np.broadcast_to(np.minimum(k_eff, Lk), (B * H, Lq)))
+    s = sc.cpu().numpy().reshape(B * H, Lq, k)
+    assert np.array_equal(np.isneginf(s), g < 0)
+    assert torch.equal(parity.run_attn(w, x, debug=False), out)
+
+
+@pytest.mark.parametrize("dtype", [wl.BF16, wl.F32])
+@pytest.mark.parametrize("Lk,k", [(200, 64), (700, 100), (1024, 256)])
+def test_short_rows_ties(Lk, k, dtype):
+    """Scores that take four values only (keys repeated): the k-th is always tied, and the
+    lowest indices among the tied keys are kept."""
+    w = wl.WORKLOADS["c2"].scaled(B=1, H=1, Lq=40, Lk=Lk, k=k, dtype=dtype)
+    x = wl.make_inputs(w)
+    kv = x["K"].values[0, 0]
+    kv[:] = kv[np.arange(Lk) % 4]
+    x["K"] = wl._store(kv[None, None], dtype)
+    print("[case] ties", w, flush=True)
+    out, idx, _ = parity.run_attn(w, x)
+    s = x["Q"].values[0, 0].astype(np.float64) @ kv[:4].astype(np.float64).T
+    g = idx.cpu().numpy()[0, 0]
+    for i in range(w.Lq):
+        order = sorted(range(Lk), key=lambda j: (-s[i, j % 4], j))[:k]
+        assert g[i].tolist() == order
+    parity.check_attn(w, x, out, idx)
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_short_rows_value_rows_not_finite(dtype):
+    """Unselected value rows that are infinite or NaN do not reach the output; a selected
+    one does, in its column only."""
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    q, k, v = (torch.randn(1, 2, n, 64, generator=gen, device="cuda").to(dtype) for n in (50, 300, 300))
+    ref, idx, _ = tk.attn(q, k, v, 8, cache=True)
+    used = torch.zeros(2, 300, dtype=torch.bool, device="cuda")
+    for h in range(2):
+        used[h, idx[0, h].flatten().long()] = True
+    free = (~used[0]).nonzero().flatten()
+    assert free.numel() >= 2
+    v2 = v.clone()
+    v2[0, 0, free[0]] = float("inf")
+    v2[0, 0, free[1]] = float("nan")
+    got = tk.attn(q, k, v2, 8)
+    tol = 2e-2 if dtype == torch.bfloat16 else 1e-5
+    assert torch.isfinite(got).all()
+    assert ((got - ref).abs().max(-1).values <= tol * ref.abs().max(-1).values).all()
+    v3 = v2.clone()
+    v3[0, 1, idx[0, 1, 0, 0].long(), 5] = float("inf")
+    got = tk.attn(q, k, v3, 8)
+    bad = ~torch.isfinite(got)
+    rows = (idx[0, 1] == idx[0, 1, 0, 0]).any(-1)
+    want = torch.zeros_like(bad)
+    want[0, 1, :, 5] = rows
+    assert torch.equal(bad, want)
