@@ -256,9 +256,11 @@ int topk_profile_end(double* stage_ms, int64_t* stage_launches, int n_stages);
  * keys selected by no row get zeros. All tensors are caller-owned device memory,
  * contiguous, in `dtype` (fp32 accumulation; bf16 results rounded to nearest even);
  * every output element is written. Entries of top_idx outside [0, Lk) are padding.
- * The sums over a key's rows run in increasing (row, slot) order, so results do
- * not depend on scheduling (with atomic lists, see topk_set_backward_lists, only
- * for keys that at most 1024 rows selected). Workspace:
+ * The sums over a key's rows run in increasing (row, slot) order, or, where the
+ * gradients are matrix products over cells of 64 rows x 64 keys (bf16 rows that keep a
+ * large share of the keys, see topk_set_backward_lists), in a fixed order of cells, so
+ * results do not depend on scheduling (with atomic lists only for keys that at most
+ * 1024 rows selected). Workspace:
  * topk_attn_backward_workspace_bytes() bytes, O(B*H*(Lq*k + Lk)) (the registered
  * workspace, or one allocated on the stream). Errors as topk_attn; additionally
  * TOPK_E_UNSUPPORTED when B*H*Lq*k or B*H*Lk reaches 2^31.
@@ -280,8 +282,11 @@ int topk_ffn_backward(const void* X, const void* W1, const void* W2, const int32
 
 /*
  * How the backward calls group the selected (row, key) pairs by key, process-wide:
- * TOPK_LISTS_AUTO (default) takes the bucket sort for heads of up to 2^19 keys
- * and atomic counters beyond; TOPK_LISTS_BUCKET asks for the bucket sort (a
+ * TOPK_LISTS_AUTO (default) takes cells of 64 rows x 64 keys and matrix products (bf16,
+ * rows of d >= 256 that keep at least one key in 40, narrower ones under tighter rules),
+ * otherwise the bucket sort for heads of up to 2^19 keys and atomic counters beyond; a
+ * call whose registered workspace holds the lists but not the cells takes the lists.
+ * TOPK_LISTS_BUCKET asks for the bucket sort (a
  * backward call on a larger head then fails with TOPK_E_UNSUPPORTED);
  * TOPK_LISTS_ATOMIC asks for the atomic counters. The bucket sort (a two-level
  * stable counting sort in LDS) writes every list in increasing pair order; atomic

@@ -491,6 +491,30 @@ size_t bwd_bytes(const BwdProblem& bp) {
   return total;
 }
 
+// the same by cells
+size_t cell_carve(const BwdProblem& bp, char* ws, CellBufs* cb) {
+  const int64_t npairs = bp.BH * bp.Lq * bp.k;
+  const CellLayout L = cell_layout(bp);
+  size_t off = 0;
+  auto take = [&](size_t bytes) {
+    char* p = ws ? ws + off : nullptr;
+    off += up(bytes);
+    return p;
+  };
+  cb->nstrip = L.nstrip;
+  cb->ncell = L.ncell;
+  cb->off_row = L.off_row;
+  cb->seen = (int)(64 * L.ncell * 2);
+  cb->split_q = L.split_q;
+  cb->split_k = L.split_k;
+  cb->off = (int32_t*)take((size_t)(bp.BH * L.nstrip * L.off_row) * 4);
+  cb->ent = (uint32_t*)take((size_t)npairs * 4);
+  cb->a = (float*)take((size_t)npairs * 4);
+  cb->w = (float*)take((size_t)npairs * 4);
+  cb->part = (float*)take((size_t)L.part_floats * 4);
+  return off;
+}
+
 BwdBufs bwd_carve(const BwdProblem& bp, char* ws) {
   const int64_t nkeys = bp.BH * bp.Lk, npairs = bp.BH * bp.Lq * bp.k;
   BwdBufs b{};
@@ -556,8 +580,18 @@ int bwd_problem(BwdProblem* bp, const void* Q, const void* K, const void* V, con
   return TOPK_OK;
 }
 
+size_t cell_bytes(const BwdProblem& bp) {
+  CellBufs cb;
+  return cell_carve(bp, nullptr, &cb);
+}
+
 int run_backward(const BwdProblem& bp, hipStream_t st) {
-  const size_t need = bwd_bytes(bp);
+  bool cells = cells_ok(bp);
+  size_t need = cells ? cell_bytes(bp) : bwd_bytes(bp);
+  if (cells && g_ws && need > g_ws_bytes) {  // a workspace too small for the cells may do for the lists
+    cells = false;
+    need = bwd_bytes(bp);
+  }
   char* ws = (char*)g_ws;
   bool own = false;
   if (g_ws) {
@@ -572,7 +606,13 @@ int run_backward(const BwdProblem& bp, hipStream_t st) {
   hipError_t e;
   {
     StageTimer t(st, ST_BWD);
-    e = launch_backward(bp, bwd_carve(bp, ws), st);
+    if (cells) {
+      CellBufs cb;
+      cell_carve(bp, ws, &cb);
+      e = launch_backward_cells(bp, cb, st);
+    } else {
+      e = launch_backward(bp, bwd_carve(bp, ws), st);
+    }
   }
   if (own) hipFreeAsync(ws, st);
   if (e != hipSuccess) return fail(TOPK_E_HIP, "kernel launch failed: %s", hipGetErrorString(e));
@@ -847,7 +887,7 @@ size_t topk_attn_backward_workspace_bytes(int64_t B, int64_t H, int64_t Lq, int6
   if (bwd_problem(&bp, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, B * H, Lq,
                   Lk, d, k, Lk * d, 1.f, dtype, ACT_SOFTMAX, false))
     return 0;
-  return bwd_bytes(bp);
+  return cells_ok(bp) ? cell_bytes(bp) : bwd_bytes(bp);
 }
 
 size_t topk_ffn_backward_workspace_bytes(int64_t N, int64_t d_model, int64_t d_ff, int64_t k, int dtype) {
@@ -855,7 +895,7 @@ size_t topk_ffn_backward_workspace_bytes(int64_t N, int64_t d_model, int64_t d_f
   if (bwd_problem(&bp, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, 1, N, d_ff,
                   d_model, k, 0, 1.f, dtype, ACT_RELU, false))
     return 0;
-  return bwd_bytes(bp);
+  return cells_ok(bp) ? cell_bytes(bp) : bwd_bytes(bp);
 }
 
 int topk_set_memory_budget(size_t bytes) {

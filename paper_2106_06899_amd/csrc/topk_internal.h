@@ -75,6 +75,12 @@ struct PassBufs {
                       // filtered tile GEMM); 0: two lists of caph, lengths cnt[2p], cnt[2p + 1]
   float* samp;        // filtered path: [rows, ceil(Lk / FILTER_KSTRIDE)] sampled scores
   float* thr;         // filtered path: [rows] thresholds
+  // k_tile_scores_mfma<3>, the backward pass's products: the pairs in cell order
+  const int32_t* cell_off;
+  const uint32_t* cell_ent;
+  const float* cell_w;
+  float* cell_val;
+  int64_t nstrip, ncell, off_row;
 };
 
 struct ScanCfg {
@@ -178,6 +184,45 @@ struct BwdBufs {
 };
 
 hipError_t launch_backward(const BwdProblem& bp, const BwdBufs& b, hipStream_t st);
+
+// Backward pass by cells of 64 rows x 64 keys (topk_cells.hip).
+constexpr int CELL_MAX = 256;  // cells along a head's keys: a strip's bitmap takes 128 KB of LDS
+struct CellLayout {
+  int64_t nstrip, ncell;        // strips of 64 rows and cells of 64 keys per head
+  int64_t off_row;              // words per strip of its ranges and its mark
+  int split_q, split_k;         // parts of the d_Q products, and of the d_K and d_V products
+  int64_t part_floats;          // their partial sums
+};
+struct CellBufs {
+  int64_t nstrip, ncell, off_row;
+  int seen;        // words of a strip's (row, key) bitmap
+  int split_q, split_k;
+  int32_t* off;    // [BH * nstrip][off_row]: each cell's range of ent
+  uint32_t* ent;   // [rows * k] in cell order: local row << 6 | local key
+  float* w;        // cell order: the weights
+  float* a;        // cell order: d_out . V[j], then the score gradients
+  float* part;     // partial sums of split products
+};
+CellLayout cell_layout(const BwdProblem& bp);
+// d_out . V[j] of every pair into cb.a (the score GEMMs of topk_kernels.hip)
+hipError_t launch_cells_products(const BwdProblem& bp, const CellBufs& cb, hipStream_t st);
+hipError_t launch_backward_cells(const BwdProblem& bp, const CellBufs& cb, hipStream_t st);
+
+// Where the products by cells take the place of the gathers by lists (bf16, automatic
+// lists). The gathers' time goes with the pairs and the row size, the products' with rows
+// x keys; each cell also costs them a fixed 2000 to 5000 cycles, which wide rows hide.
+// Measured (us, lists / cells): d >= 256: keys per kept key 8: 5290 / 1040, 16: 5570 /
+// 1650, 32: 6230 / 2760 and (d 256) 410 / 306, 43: 4710 / 2650, 64: 690 / 675. d = 128: 16:
+// 390 / 256 (causal 370 / 325), 32: 760 / 705 and (8192 causal) 1540 / 1780; a head of 700
+// rows 50 / 63: too few workgroups. d = 64 pays only on short rows, whose lists are dearer:
+// 48 heads of 1024, 16: 264 / 195; 12 heads of 2048, 16: 196 / 210.
+inline bool cells_ok(const BwdProblem& bp) {
+  if (bp.list_mode != 0 || bp.dtype != T_BF16 || bp.d % 32 != 0 || bp.Lk > (int64_t)64 * CELL_MAX) return false;
+  if (bp.d >= 256) return bp.Lk <= 40 * bp.k;
+  const int64_t tiles = bp.BH * ((bp.Lq + 127) / 128);
+  if (bp.d >= 128) return bp.Lk <= 16 * bp.k && tiles >= 128;
+  return bp.d == 64 && bp.Lk <= 1024 && bp.Lk <= 16 * bp.k && tiles >= 256;
+}
 hipError_t launch_filter(const Problem& pb, const Pass& ps, const PassBufs& b, int stage, hipStream_t st);
 hipError_t launch_filter_scan(const Problem& pb, const Pass& ps, const PassBufs& b, hipStream_t st);
 

@@ -259,7 +259,9 @@ __global__ __launch_bounds__(256) void k_tile_scores(Problem pb, Pass ps, float*
 // MODE 0 writes the tile; MODE 1 scores every FILTER_KSTRIDE-th key only (the
 // filtered path's sample, "keys" of the grid are sample slots); MODE 2 appends the
 // scores at or above each row's threshold to the row's candidate list instead of
-// writing the tile.
+// writing the tile; MODE 3 (the backward pass by cells, d_out and V in the places of Q
+// and K) gives each listed pair of the tile its product, 128 keys of the tile at a time
+// through LDS, and skips tiles without pairs.
 constexpr int TSM_TQ = 128, TSM_TK = 256;
 
 template <int MODE>
@@ -268,7 +270,8 @@ __global__ __launch_bounds__(256, 2) void k_tile_scores_mfma(Problem pb, Pass ps
   constexpr int TQ = TSM_TQ, TK = TSM_TK, KS = 32;  // tile rows, tile keys, features per slice
   constexpr int QBYTES = TQ * KS * 2, KBYTES = TK * KS * 2;
   constexpr int QLPW = QBYTES / 1024 / 4, KLPW = KBYTES / 1024 / 4;  // 1 KB loads per wave
-  __shared__ __attribute__((aligned(16))) unsigned char sm[2][QBYTES + KBYTES];
+  // (MODE 3 holds 128 x 128 products there, 132 floats a row)
+  __shared__ __attribute__((aligned(16))) unsigned char sm[2][MODE == 3 ? 128 * 132 * 2 : QBYTES + KBYTES];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, half = lane >> 5, n = lane & 31;
   // Workgroup order: query tiles fastest, then key tiles, then chunks, renumbered
   // so each XCD runs a contiguous range. The query tiles of one chunk then read
@@ -285,6 +288,36 @@ __global__ __launch_bounds__(256, 2) void k_tile_scores_mfma(Problem pb, Pass ps
   if (pb.causal) {
     const int64_t last = r0 + TQ - 1 < pb.C ? r0 + TQ - 1 : pb.C - 1;
     if (key0 * KSTEP > i0 + last) return;
+  }
+  const int64_t strip0 = bh * bufs.nstrip + r0 / 64, cell0 = key0 / 64;  // MODE 3
+  auto cell_range = [&](int64_t h, int64_t cell, int ncells, int32_t* beg, int32_t* end) {
+    const bool in = r0 / 64 + h < bufs.nstrip && cell < bufs.ncell;
+    const int32_t* o = bufs.cell_off + (in ? (strip0 + h) * bufs.off_row + cell : 0);
+    const int64_t upto = cell + ncells < bufs.ncell ? ncells : bufs.ncell - cell;
+    *beg = in ? o[0] : 0;
+    *end = in ? o[upto] : 0;
+  };
+  // MODE 3: the lists of the tile's halves (cells cell0 + 2 j and the next, contiguous per
+  // strip h), and this thread's first entries of each, on their way during the contraction
+  int32_t l_beg[2][2], l_mid[2][2], l_end[2][2];
+  uint32_t l_e0[2][2];
+  if (MODE == 3) {
+    int32_t pairs = 0;
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        int32_t x;
+        cell_range(h, cell0 + 2 * j, 1, &l_beg[j][h], &l_mid[j][h]);
+        cell_range(h, cell0 + 2 * j, 2, &x, &l_end[j][h]);
+        pairs += l_end[j][h] - l_beg[j][h];
+      }
+    if (pairs == 0) return;
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        l_e0[j][h] = l_beg[j][h] + tid < l_end[j][h] ? bufs.cell_ent[l_beg[j][h] + tid] : 0u;
   }
   const int64_t d = pb.d;
   const uint16_t* Qb = (const uint16_t*)pb.Q;
@@ -424,6 +457,37 @@ __global__ __launch_bounds__(256, 2) void k_tile_scores_mfma(Problem pb, Pass ps
           const float x = stash[j * 64 + lane];
           if (pos < cap) dst[pos] = ((uint64_t)__float_as_uint(x) << 32) | (uint64_t)(nk0 - (j + (j & ~3u)));
           ++pos;
+        }
+      }
+    }
+    return;
+  }
+  if (MODE == 3) {
+    constexpr int TS = 132;  // row stride of the 128 x 128 products in LDS
+    static_assert(MODE != 3 || TQ * TS * 4 <= sizeof(sm), "the products fit the operand buffers");
+    float* T = (float*)&sm[0][0];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      __syncthreads();  // the operands, or the previous products, have been read
+      if ((wave & 1) == j) {
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+          for (int b = 0; b < 4; ++b)
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+              *(float4*)&T[(wq + a * 32 + n) * TS + b * 32 + 8 * u + 4 * half] =
+                  make_float4(acc[a][b][4 * u], acc[a][b][4 * u + 1], acc[a][b][4 * u + 2], acc[a][b][4 * u + 3]);
+      }
+      __syncthreads();
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        uint32_t e = l_e0[j][h];
+        for (int32_t i = l_beg[j][h] + tid; i < l_end[j][h]; i += 256) {
+          const uint32_t en = i + 256 < l_end[j][h] ? bufs.cell_ent[i + 256] : 0u;
+          const float x = T[((e >> 6) + 64 * h) * TS + (e & 63) + (i < l_mid[j][h] ? 0 : 64)];
+          bufs.cell_val[i] = pb.act == ACT_SOFTMAX || bufs.cell_w[i] > 0.f ? x : 0.f;  // ReLU passes where its weight is positive
+          e = en;
         }
       }
     }
@@ -2915,6 +2979,31 @@ static void scan_in_place(int32_t* a, int64_t n, int32_t* sums, hipStream_t st) 
   k_bwd_scan_local<<<(unsigned)nb, 256, 0, st>>>(a, n, sums);
   k_bwd_scan_sums<<<1, 256, 0, st>>>(sums, nb);
   k_bwd_scan_add<<<(unsigned)nb, 256, 0, st>>>(a, n, sums);
+}
+
+hipError_t launch_cells_products(const BwdProblem& bp, const CellBufs& cb, hipStream_t st) {
+  Problem pb{};
+  pb.Q = bp.dout;
+  pb.K = bp.V;
+  pb.BH = bp.BH;
+  pb.Lq = pb.q1 = pb.C = bp.Lq;  // one chunk per head
+  pb.Lk = bp.Lk;
+  pb.d = bp.d;
+  pb.kv_head_stride = bp.kv_head_stride;
+  pb.act = bp.act;
+  Pass ps{0, bp.BH, 1};
+  PassBufs b{};
+  b.cell_off = cb.off;
+  b.cell_ent = cb.ent;
+  b.cell_w = cb.w;
+  b.cell_val = cb.a;
+  b.nstrip = cb.nstrip;
+  b.ncell = cb.ncell;
+  b.off_row = cb.off_row;
+  const int64_t g = ((bp.Lk + TSM_TK - 1) / TSM_TK) * ((bp.Lq + 127) / 128) * bp.BH;
+  if (g > 0x7FFFFFFF || bp.dtype != T_BF16 || bp.d % 32 != 0) return hipErrorInvalidValue;
+  k_tile_scores_mfma<3><<<(unsigned)g, 256, 0, st>>>(pb, ps, b);
+  return hipGetLastError();
 }
 
 hipError_t launch_backward(const BwdProblem& bp, const BwdBufs& b, hipStream_t st) {

@@ -1,0 +1,141 @@
+"""GPU tests of the backward pass by cells (64 x 64 blocks of selected pairs expanded into
+matrix products): against the fp64 oracle at the edges of its strips, cells and tiles and
+with split products; equal to the gathers by lists within rounding; keys listed twice in a
+row, padding, and rows that are not finite."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2106_06899_amd as tk
+from oracle import topk_backward as bo
+from paper_2106_06899_amd import workloads as wl
+from tests import parity
+
+pytestmark = pytest.mark.gpu
+
+
+def _lists(fn):
+    tk.set_backward_lists(tk.TOPK_LISTS_BUCKET)
+    try:
+        return fn()
+    finally:
+        tk.set_backward_lists(tk.TOPK_LISTS_AUTO)
+
+
+def _close(a, b):
+    """Two bf16 results of the same sums in different orders: neighbouring bf16 numbers at
+    most, which lie up to 2^-7 of their size apart; held to each row's largest entry."""
+    a, b = a.float(), b.float()
+    tol = 2.0 ** -7 * b.abs().amax(-1, keepdim=True) + 1e-6 * b.abs().max()
+    assert bool(((a - b).abs() <= tol).all()), float(((a - b).abs() / tol.clamp_min(1e-30)).max())
+
+
+# rows around the 64-row strips and 128-row tiles, units around the 64-key cells (4096 units
+# of few rows split the products); column tiles of 256 that d fills, half fills and repeats
+FFN_CASES = [(1, 256, 64, 2), (63, 768, 300, 40), (65, 288, 129, 129), (130, 1024, 513, 20), (300, 512, 4096, 128),
+             (257, 256, 2000, 512)]
+
+
+@pytest.mark.parametrize("case", FFN_CASES)
+def test_ffn_cells(case):
+    N, dm, dff, k = case
+    w = wl.WORKLOADS["c5"].scaled(N=N, d_model=dm, d_ff=dff, k=k, chunk=64)
+    print("[case]", w, flush=True)
+    x = wl.make_inputs(w)
+    a, b1, b2 = (parity.to_dev(x[n]) for n in ("X", "W1", "W2"))
+    _, idx, dots = tk.ffn(a, b1, b2, k, w.chunk, cache=True)
+    g = parity.grad_out((N, dm), w.dtype, 31)
+    got = tk.ffn_backward(a, b1, b2, idx, dots, parity.to_dev(g))
+    ref, mag = bo.oracle_ffn_backward(x["X"].values, x["W1"].values, x["W2"].values, idx.cpu().numpy(), g.values,
+                                      chunk=64, magnitudes=True)
+    for n, p, r, m in zip(("d_X", "d_W1", "d_W2"), got, ref, mag):
+        parity.check_grad_rows(n, p, r, m, w.dtype)
+
+
+# enough heads for the rules of d = 128 (128 tiles) and d = 64 (256 tiles)
+ATTN_CASES = [(8, 16, 70, 90, 128, 20, False), (8, 16, 70, 70, 128, 20, True), (16, 16, 65, 65, 64, 9, True),
+              (4, 8, 500, 130, 128, 100, False), (2, 128, 33, 40, 160, 40, False)]
+
+
+@pytest.mark.parametrize("case", ATTN_CASES)
+def test_attention_cells(case):
+    B, H, Lq, Lk, d, k, causal = case
+    w = wl.WORKLOADS["c4"].scaled(B=B, H=H, Lq=Lq, Lk=Lk, d=d, k=k, causal=causal, scale=float(np.float32(d ** -0.5)))
+    print("[case]", w, flush=True)
+    x = wl.make_inputs(w)
+    q, kk, v = (parity.to_dev(x[n]) for n in ("Q", "K", "V"))
+    _, idx, dots = tk.attn(q, kk, v, k, 64, causal, w.scale, cache=True)
+    g = parity.grad_out((B, H, Lq, d), w.dtype, 32)
+    gd = parity.to_dev(g)
+    got = tk.attn_backward(q, kk, v, idx, dots, gd, w.scale)
+    again = tk.attn_backward(q, kk, v, idx, dots, gd, w.scale)
+    for p, r in zip(got, again):
+        assert torch.equal(p, r)
+    hs = [0, H // 2, H - 1]  # three heads of the last batch against the oracle
+    sub = [t.values[-1:, hs] for t in (x["Q"], x["K"], x["V"])]
+    ref, mag = bo.oracle_attn_backward(*sub, idx[-1:, hs].cpu().numpy(), g.values[-1:, hs], w.scale, chunk=64, magnitudes=True)
+    for n, p, r, m in zip(("d_Q", "d_K", "d_V"), got, ref, mag):
+        parity.check_grad_rows(n, p[-1:, hs], r, m, w.dtype)
+    for p, r in zip(got, _lists(lambda: tk.attn_backward(q, kk, v, idx, dots, gd, w.scale))):
+        _close(p, r)
+
+
+def test_cells_keys_listed_twice_and_padding():
+    """A caller's own index lists: keys repeated in a row add up, entries outside the keys
+    are padding; as by lists."""
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    x, g = (torch.randn(200, 256, generator=gen, device="cuda").bfloat16() for _ in range(2))
+    w1, w2 = (torch.randn(500, 256, generator=gen, device="cuda").bfloat16() for _ in range(2))
+    idx = torch.randint(-3, 520, (200, 40), generator=gen, device="cuda", dtype=torch.int32)
+    idx[:64] = torch.stack([torch.randperm(500, generator=gen, device="cuda")[:40] for _ in range(64)]).int()  # a strip without repeats
+    dots = torch.randn(200, 40, generator=gen, device="cuda")
+    got = tk.ffn_backward(x, w1, w2, idx, dots, g)
+    for p, r in zip(got, _lists(lambda: tk.ffn_backward(x, w1, w2, idx, dots, g))):
+        _close(p, r)
+
+
+@pytest.mark.parametrize("N,dff", [(400, 1000), (140, 4000)])  # whole products, split products
+def test_cells_rows_not_finite(N, dff):
+    """An infinite row of d_out reaches its own d_X row and the units its token kept, nothing
+    else; the rest is what it is without it."""
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    x, g = (torch.randn(N, 256, generator=gen, device="cuda").bfloat16() for _ in range(2))
+    w1, w2 = (torch.randn(dff, 256, generator=gen, device="cuda").bfloat16() for _ in range(2))
+    _, idx, dots = tk.ffn(x, w1, w2, 100, cache=True)
+    ref = _lists(lambda: tk.ffn_backward(x, w1, w2, idx, dots, g))
+    bad = g.clone()
+    bad[70] = float("inf")
+    got = tk.ffn_backward(x, w1, w2, idx, dots, bad)
+    lst = _lists(lambda: tk.ffn_backward(x, w1, w2, idx, dots, bad))
+    for p, q, r in zip(got, lst, ref):
+        fin = torch.isfinite(q).all(-1)
+        assert torch.equal(torch.isfinite(p).all(-1), fin)
+        assert 0 < int((~fin).sum()) < p.shape[0]
+        _close(p[fin], r[fin])
+
+
+def test_cells_need_more_workspace_than_lists():
+    """A registered workspace that holds the lists but not the cells is still enough."""
+    L = tk.lib()
+    gen = torch.Generator(device="cuda").manual_seed(6)
+    x, g = (torch.randn(512, 1024, generator=gen, device="cuda").bfloat16() for _ in range(2))
+    w1, w2 = (torch.randn(4096, 1024, generator=gen, device="cuda").bfloat16() for _ in range(2))
+    _, idx, dots = tk.ffn(x, w1, w2, 128, cache=True)
+    cells = L.topk_ffn_backward_workspace_bytes(512, 1024, 4096, 128, tk.TOPK_BF16)
+    lists = _lists(lambda: L.topk_ffn_backward_workspace_bytes(512, 1024, 4096, 128, tk.TOPK_BF16))
+    assert cells > lists  # split products
+    want = _lists(lambda: tk.ffn_backward(x, w1, w2, idx, dots, g))
+    out = [torch.empty_like(t) for t in (x, w1, w2)]
+    ws = torch.empty(lists, dtype=torch.uint8, device="cuda")
+    tk._raise(L.topk_set_workspace(ctypes.c_void_p(ws.data_ptr()), lists))
+    try:
+        tk._raise(L.topk_ffn_backward(x.data_ptr(), w1.data_ptr(), w2.data_ptr(), idx.data_ptr(), dots.data_ptr(), g.data_ptr(),
+                                      out[0].data_ptr(), out[1].data_ptr(), out[2].data_ptr(), 512, 1024, 4096, 128, tk.TOPK_BF16,
+                                      ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)))
+    finally:
+        L.topk_set_workspace(None, 0)
+    torch.cuda.synchronize()
+    for p, r in zip(out, want):
+        assert torch.equal(p, r)
