@@ -220,7 +220,9 @@ const char* topk_last_error(void);
  * d % 32 == 0, k <= 512, 2048 < Lk <= 65536: every 16th key is scored first, each
  * row's threshold comes from those samples, and only the scores reaching it are kept
  * as candidates, by the fused path's score kernel at d = 128 and by the chunk-tile
- * GEMM otherwise; the rest as the fused path), or a negative status for invalid
+ * GEMM otherwise; the rest as the fused path). Calls of a few queries per head against
+ * 1025 to 65536 keys (bf16, at most 128 queries, k <= 512) run as path 2 with kernels of
+ * their own that spread the keys. Or a negative status for invalid
  * arguments. For tests and reports.
  */
 int topk_attn_path(int64_t B, int64_t H, int64_t Lq, int64_t Lk, int64_t d,

@@ -75,6 +75,7 @@ enum Path { PATH_FUSED = 1, PATH_TILE = 2, PATH_FILTER = 4 };
 
 struct Plan {
   int path;
+  bool few;  // PATH_TILE by the few-query kernels
   ScanCfg scan;
   int64_t nchunk, total_chunks, per_pass;
   size_t per_chunk, fixed;
@@ -136,7 +137,24 @@ bool filter_ok(const Problem& pb) {
 // candidates kept per (row, half) of the list buffers
 int64_t caph_for(const Problem& pb, int path) { return path == PATH_FILTER && pb.k > 256 ? 2 * FUSED_CAPH : FUSED_CAPH; }
 
-void choose_path(const Problem& pb, Plan* pl) {
+// Few queries per head (bf16): the scores of all its queries in workspace, whatever the
+// chunk size (at most 128 rows of 65536 scores, less than the fallback rows that the
+// fused and filtered paths keep). k up to 512 and, so that the block maxima's bound is a
+// sharp one, at least five blocks of 16 keys per four kept. The scan takes as long for 1 as
+// for 256 queries of a head (0.7 us per 64 keys at d = 64, 1.3 at d = 128); writing the
+// scores takes 1 us per 10^6, so 8192 rows in all are where the two meet. The filtered and
+// tiled GEMMs use 128-query tiles over all keys and lose less: 2048 rows.
+// Measured (us, before / now): 64 heads x 5 queries, 20001 keys, d 128, k 128: 442 / 103; 8 x
+// 1, 60000, d 64: 714 / 40; 64 x 64, 20001, d 64: 458 / 169; 128 x 64, 4096, d 64: 107 / 97; 256
+// x 128, 2048, d 64 (tiled): 195 / 228; 64 x 128, 9000, d 96 (filtered): 167 / 191; feed-forward
+// 24 tokens, 768, 16384 units, k 256: 115 / 41; 128, 1024, 32768, k 512: 140 / 98.
+bool few_ok(const Problem& pb, int path) {
+  return pb.dtype == T_BF16 && pb.d % 32 == 0 && !pb.causal && !pb.tile_only && pb.Lq <= FEW_ROWS && pb.q0 == 0 &&
+         pb.q1 == pb.Lq && pb.Lk > ROWS_MAX_LK && pb.Lk <= 65536 && pb.k <= 512 && 4 * ((pb.Lk + 15) / 16) >= 5 * pb.k &&
+         (path != PATH_TILE || pb.C >= pb.Lq) && pb.BH * pb.Lq <= (path == PATH_FUSED ? 8192 : 2048);
+}
+
+void choose_long_path(const Problem& pb, Plan* pl) {
   pl->path = PATH_TILE;
   pl->scan = {MODE_SAMPLE, 16, 12, 2, 0, 0};
   if (pb.tile_only) {
@@ -172,9 +190,22 @@ void choose_path(const Problem& pb, Plan* pl) {
   }
 }
 
+void choose_path(const Problem& pb, Plan* pl) {
+  choose_long_path(pb, pl);
+  pl->few = few_ok(pb, pl->path);
+  if (pl->few) pl->path = PATH_TILE;
+}
+// the path, and the problem as that path runs it
+void choose_path_for(Problem* pb, Plan* pl) {
+  choose_path(*pb, pl);
+  if (pl->few) pb->C = pb->Lq;
+}
+
 size_t row_bytes(const Problem& pb, const Plan& pl) {
   size_t b = (size_t)pb.k * 8 + 4;  // selection + redo list entry
-  if (pl.path == PATH_TILE)
+  if (pl.few)
+    b += (size_t)few_row_len(pb.Lk) / 16 * 68;  // scores and block maxima
+  else if (pl.path == PATH_TILE)
     b += (size_t)pb.Lk * 4;
   else
     b += 2 * (size_t)caph_for(pb, pl.path) * 8 + 8;
@@ -216,7 +247,11 @@ PassBufs carve(const Problem& pb, const Plan& pl, char* ws) {
   off += up(rows * 4);
   b.sel = (uint64_t*)(ws + off);
   off += up(rows * (size_t)pb.k * 8);
-  if (pl.path == PATH_TILE) {
+  if (pl.few) {
+    b.scores = (float*)(ws + off);
+    off += up(rows * (size_t)few_row_len(pb.Lk) * 4);
+    b.blk = (uint32_t*)(ws + off);
+  } else if (pl.path == PATH_TILE) {
     b.scores = (float*)(ws + off);
     off += up(rows * (size_t)pb.Lk * 4);
   } else {
@@ -291,7 +326,7 @@ int run(Problem whole, hipStream_t st, bool report, void* fixed_ws = nullptr, si
   const size_t ws_given_bytes = fixed_ws ? fixed_bytes : g_ws_bytes;
   size_t budget = ws_given ? ws_given_bytes : g_budget.load(std::memory_order_relaxed), need = 0;
   for (int q = 0; q < np; ++q) {
-    choose_path(parts[q], &plans[q]);
+    choose_path_for(&parts[q], &plans[q]);
     plan_sizes(parts[q], &plans[q], budget);
     const size_t n = plan_total(plans[q], parts[q]);
     need = n > need ? n : need;
@@ -341,14 +376,14 @@ int run(Problem whole, hipStream_t st, bool report, void* fixed_ws = nullptr, si
         e = launch_redo(pb, ps, b, st);
       }
     } else if (pl.path == PATH_TILE) {
-      if (e == hipSuccess) e = launch_init(b, st);
+      if (e == hipSuccess && !pl.few) e = launch_init(b, st);
       if (e == hipSuccess) {
         StageTimer t(st, ST_SCORE);
-        e = launch_tile_scores(pb, ps, b, st);
+        e = pl.few ? launch_few_scores(pb, ps, b, st) : launch_tile_scores(pb, ps, b, st);
       }
       if (e == hipSuccess) {
         StageTimer t(st, ST_SELECT);
-        e = launch_tile_select(pb, ps, b, st);
+        e = pl.few ? launch_few_select(pb, ps, b, st) : launch_tile_select(pb, ps, b, st);
       }
     } else {
       if (e == hipSuccess) e = launch_init(b, st);
@@ -470,7 +505,7 @@ size_t workspace_for(const Problem& whole) {
   size_t need = 0;
   for (int q = 0; q < np; ++q) {
     Plan pl;
-    choose_path(parts[q], &pl);
+    choose_path_for(&parts[q], &pl);
     plan_sizes(parts[q], &pl, budget);
     const size_t n = plan_total(pl, parts[q]);
     need = n > need ? n : need;

@@ -54,6 +54,10 @@ __device__ __forceinline__ void wave_sync_lds() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// lanes of m below this one
+__device__ __forceinline__ uint32_t lanes_below(uint64_t m) {
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
 // The value of lane (lane ^ m), m a power of two known at compile time once the
 // caller is unrolled: m = 1, 2 by a DPP quad permutation (no LDS traffic), m = 4..16
 // by a bit-mode ds_swizzle (xor within 32 lanes), m = 32 by ds_bpermute.

@@ -73,6 +73,7 @@ struct PassBufs {
   int64_t caph;
   int cand_single;    // one list of up to 2 caph per row, its length in cnt[2p] (fused scan,
                       // filtered tile GEMM); 0: two lists of caph, lengths cnt[2p], cnt[2p + 1]
+  uint32_t* blk;      // few queries: [rows, few_row_len / 16] largest score of every 16 keys, as keys
   float* samp;        // filtered path: [rows, ceil(Lk / FILTER_KSTRIDE)] sampled scores
   float* thr;         // filtered path: [rows] thresholds
   // k_tile_scores_mfma<3>, the backward pass's products: the pairs in cell order
@@ -103,6 +104,12 @@ inline bool rows_ok(const Problem& pb) {
          (pb.d == 32 || pb.d == 64 || pb.d == 96 || pb.d == 128);
 }
 hipError_t launch_rows(const Problem& pb, hipStream_t st);
+
+// Few queries (k_few_scores, k_few_select): their score rows are padded to whole blocks of 16.
+constexpr int64_t FEW_ROWS = 128;
+__host__ __device__ inline int64_t few_row_len(int64_t Lk) { return (Lk + 15) / 16 * 16; }
+hipError_t launch_few_scores(const Problem& pb, const Pass& ps, const PassBufs& b, hipStream_t st);
+hipError_t launch_few_select(const Problem& pb, const Pass& ps, const PassBufs& b, hipStream_t st);
 
 hipError_t launch_init(const PassBufs& b, hipStream_t st);
 hipError_t launch_tile_scores(const Problem& pb, const Pass& ps, const PassBufs& b, hipStream_t st);

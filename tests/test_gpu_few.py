@@ -1,0 +1,87 @@
+"""GPU tests of the few-query kernels (at most 128 bf16 queries per head, 1025 to 65536
+keys): against the fp64 oracle at the edges of their row groups, key blocks and lists,
+with equal scores (the fallback), and independent of the chunk size; and of the finalize
+that gives few rows eight waves each."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2106_06899_amd as tk
+from paper_2106_06899_amd import workloads as wl
+from tests import parity
+
+pytestmark = pytest.mark.gpu
+
+# (B, H, Lq, Lk, d, k): row groups of 16, 32 and 64; ragged 16-key blocks; 16 and 64 keys a
+# wave; block lists of 8 to 64 per lane; features beyond one step; k around the list sizes
+CASES = [(1, 1, 1, 1025, 64, 1), (1, 3, 16, 1040, 128, 50), (2, 2, 17, 2047, 32, 52), (1, 2, 32, 9000, 64, 128),
+         (2, 16, 33, 4099, 128, 64), (1, 8, 64, 20001, 96, 256), (1, 1, 65, 33000, 64, 257), (1, 2, 128, 17000, 160, 512),
+         (1, 2, 5, 65536, 1024, 512), (1, 4, 3, 10244, 544, 512)]
+
+
+@pytest.mark.parametrize("case", CASES)
+def test_few_queries(case):
+    B, H, Lq, Lk, d, k = case
+    w = wl.WORKLOADS["c2"].scaled(B=B, H=H, Lq=Lq, Lk=Lk, d=d, k=k, chunk=1024, scale=float(np.float32(d ** -0.5)))
+    print("[case]", w, flush=True)
+    assert tk.attn_path(B, H, Lq, Lk, d, k, w.chunk, False) == 2
+    x = wl.make_inputs(w)
+    out, idx, sc = parity.run_attn(w, x)
+    assert tk.last_fallback_rows() == 0
+    parity.check_attn(w, x, out, idx, rows=parity.sample_attn_rows(w, min(B * H * Lq, 60), seed=3))
+    g = idx.cpu().numpy().reshape(-1, k)
+    assert np.all(np.diff(np.sort(g, axis=1), axis=1) > 0) and g.min() >= 0 and g.max() < Lk
+    assert torch.equal(parity.run_attn(w, x, debug=False), out)
+
+
+@pytest.mark.parametrize("band", [0.0, 1e-30])
+def test_few_queries_equal_scores(band):
+    """Equal scores (or all below the smallest normal number apart): every block reaches
+    the bound, the rows are settled by the fallback, and the lowest indices are kept."""
+    w = wl.WORKLOADS["c2"].scaled(B=1, H=2, Lq=7, Lk=20000, k=64)
+    x = wl.make_inputs(w)
+    x["Q"] = wl._store((x["Q"].values * np.float32(band)).astype(np.float32), w.dtype)
+    print("[case] equal scores", band, w, flush=True)
+    out, idx, _ = parity.run_attn(w, x)
+    parity.check_attn(w, x, out, idx)
+    if band == 0.0:
+        assert tk.last_fallback_rows() == 14
+        assert torch.equal(idx.cpu(), torch.arange(64, dtype=torch.int32).expand(1, 2, 7, 64))
+
+
+def test_few_queries_any_chunk_and_the_fixed_scratch():
+    w = wl.WORKLOADS["c3"].scaled(H=4, Lq=40, Lk=20000, chunk=1024)
+    x = wl.make_inputs(w)
+    ref = parity.run_attn(w, x)
+    for C in (1, 7, 32):
+        print("[case] chunk", C, flush=True)
+        assert tk.attn_path(w.B, w.H, w.Lq, w.Lk, w.d, w.k, C, False) == 2
+        for a, b in zip(ref, parity.run_attn(w, x, chunk=C)):
+            assert torch.equal(a, b)
+    tk.set_memory_budget(1)  # one head per pass
+    try:
+        for a, b in zip(ref, parity.run_attn(w, x)):
+            assert torch.equal(a, b)
+    finally:
+        tk.set_memory_budget(0)
+    q, k, v = (parity.to_dev(x[n]) for n in ("Q", "K", "V"))
+    got = torch.empty_like(q)
+    tk._raise(tk.lib().topk_attn_noalloc(q.data_ptr(), k.data_ptr(), v.data_ptr(), got.data_ptr(), w.B, w.H, w.Lq, w.Lk, w.d, w.k,
+                                         w.chunk, 0, w.scale, tk.TOPK_BF16, torch.cuda.current_stream().cuda_stream))
+    torch.cuda.synchronize()
+    assert torch.equal(got, ref[0])
+
+
+@pytest.mark.parametrize("kw", [
+    dict(N=1, d_model=8, d_ff=2000, k=3), dict(N=128, d_model=96, d_ff=2048, k=512), dict(N=129, d_model=72, d_ff=1500, k=700),
+    dict(N=512, d_model=256, d_ff=3000, k=128), dict(N=24, d_model=768, d_ff=5000, k=256),
+    dict(N=60, d_model=200, d_ff=1100, k=2, dtype=wl.F32), dict(N=300, d_model=1024, d_ff=1500, k=1000, dtype=wl.F32)])
+def test_finalize_of_few_rows(kw):
+    """Column slices of 128 bytes (partial last ones), fewer and more survivors than the 64
+    row slots, in both types."""
+    w = wl.WORKLOADS["c5"].scaled(chunk=50, **kw)
+    print("[case]", w, flush=True)
+    x = wl.make_inputs(w)
+    out, idx, _ = parity.run_ffn(w, x)
+    parity.check_ffn(w, x, out, idx)
+    assert torch.equal(parity.run_ffn(w, x, debug=False), out)
