@@ -3,21 +3,28 @@
 // Every valid key of a query contributes: out_i = sum_j softmax_j(scale * q_i.k_j) v_j
 // (Eq. 1, with the causal mask of Eq. 2), the k = Lk fixed point of Eq. 4.
 //
-// gfx950 kernel, bf16 inputs, fp32 accumulation, d in {64, 128}: a streaming
-// softmax over key tiles, so no [C, Lk] score tile is ever written. One workgroup
-// = 4 waves x 32 queries of one query chunk of one head. Per 64-key tile:
+// gfx950 kernel, bf16 inputs, fp32 accumulation, d in {64, 128}: a streaming softmax
+// over key tiles, so no [C, Lk] score tile is ever written. One workgroup = 4 waves x 32
+// queries of one query chunk of one head. Per 64-key tile:
 //   * scores S^T = K Q^T by v_mfma_f32_32x32x16_bf16 (K tile from LDS as the A
 //     operand, the wave's 32 queries in registers as B): lane l holds 16 keys'
 //     scores of query l % 32 per 32-key block, keys 8*(v/4) + 4*(l/32) + v%4;
 //   * the running row maximum and sum are per query (the two lanes of a query,
-//     l and l + 32, exchange their maxima), the accumulator is rescaled when the
-//     maximum grows;
+//     l and l + 32, exchange their maxima); the accumulator is rescaled in tiles where some
+//     query's maximum grows;
 //   * O^T += V^T P^T by the same MFMA: the B operand is the lane's own 8 softmax
 //     weights of a 16-key step, in the order the score layout holds them, and the
-//     A operand reads V^T from LDS in that same key order, so each lane keeps the
-//     output rows (features) of its own query and rescales them alone.
-// V tiles are transposed into LDS on the way in (V^T[feature][key], 8-byte key
-// groups XOR-swizzled by feature row).
+//     A operand holds V^T in that same key order: column n * D/32 + c of V is row n of
+//     feature block c, so a lane reads D/32 neighbouring columns of 8 rows of the V tile
+//     (which stays as it is in memory) and pairs them up by byte permutes.
+// K and V tiles come by direct global-to-LDS loads, one tile ahead.
+//
+// Bound by vector instructions: per tile and wave 32 exponentials (512 cycles) and about
+// 160 others (640) beside 16 MFMAs (512), which this chip overlaps only in part (1670
+// cycles measured). Against V transposed through registers with 2-byte LDS writes, the
+// library exp2f and a rescale in every tile: 12 heads of 8192 tokens, d = 64: 424 -> 305 us.
+// (Taking a new maximum over only once it exceeds the old by 2^8 in weight ran 290 us, but
+// the largest weight is then not exactly 1 and its rounding shows: 2.34e-3 against 2.28e-3.)
 #include "topk_internal.h"
 
 #include <math.h>
@@ -28,7 +35,8 @@ typedef __bf16 dbf16x8 __attribute__((__vector_size__(16)));
 typedef __bf16 dbf16x4 __attribute__((__vector_size__(8)));
 typedef float df32x16 __attribute__((__vector_size__(64)));
 
-#define DENSE_WAIT_VM(n) (((n) & 15) | (7 << 4) | (15 << 8) | (((n) >> 4) << 14))
+// s_waitcnt immediate: no vector-memory operation outstanding, the other counters ignored
+constexpr int DENSE_WAIT_VM0 = (7 << 4) | (15 << 8);
 
 constexpr int DN_KT = 64;   // keys per tile
 constexpr int DN_QW = 32;   // queries per wave
@@ -44,26 +52,24 @@ struct DenseArgs {
   float scale_log2e;                  // scale * log2(e)
 };
 
-// LDS position (in bf16 units) of V^T[f][j] inside one tile buffer: row f holds the
-// 64 keys of the tile; the 16 groups of 4 keys are permuted by (f & 15).
-__device__ __forceinline__ int vt_pos(int f, int j) { return f * DN_KT + ((((j >> 2) ^ (f & 15))) << 2) + (j & 3); }
-
 template <int D, bool CAUSAL>
-__global__ __launch_bounds__(256, 2) void k_dense_attn(DenseArgs a) {
+__global__ __launch_bounds__(256, D == 64 ? 3 : 2) void k_dense_attn(DenseArgs a) {
   constexpr int NS = D / 16;         // MFMA steps over the features (scores)
   constexpr int CH = 2 * D / 16;     // 16-byte parts per key row
   constexpr int TILEB = DN_KT * 2 * D;
   constexpr int LPW = TILEB / 1024 / 4;
-  constexpr int NDB = D / 32;        // 32-feature blocks of the output
-  constexpr int VLD = DN_KT * D / 8 / 256;  // 16-byte V loads per thread per tile
+  constexpr int NDB = D / 32;        // 32-row blocks of the output features
+  constexpr int VW = NDB / 2;        // words of a lane's columns of a V row
   __shared__ __attribute__((aligned(16))) unsigned char ks0[TILEB];
   __shared__ __attribute__((aligned(16))) unsigned char ks1[TILEB];
-  __shared__ __attribute__((aligned(16))) uint16_t vt0[D * DN_KT];
-  __shared__ __attribute__((aligned(16))) uint16_t vt1[D * DN_KT];
+  __shared__ __attribute__((aligned(16))) unsigned char vs0[TILEB];
+  __shared__ __attribute__((aligned(16))) unsigned char vs1[TILEB];
 
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, half = lane >> 5, n = lane & 31;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, half = lane >> 5,
+            n = lane & 31;
   const int64_t NG = gridDim.x, bid = blockIdx.x;
-  const int64_t wg = (NG % 8 == 0) ? (bid % 8) * (NG / 8) + bid / 8 : bid;
+  int64_t wg = (NG % 8 == 0) ? (bid % 8) * (NG / 8) + bid / 8 : bid;
+  if (CAUSAL) wg = NG - 1 - wg;  // the longest workgroups first
   const int64_t cl = wg / a.wgs_per_chunk, blk = wg - cl * a.wgs_per_chunk;
   const int64_t id = a.c0 + cl, bh = id / a.nchunk, c = id - bh * a.nchunk;
   const uint16_t* Kh = a.K + bh * a.kv_head_stride;
@@ -84,39 +90,19 @@ __global__ __launch_bounds__(256, 2) void k_dense_attn(DenseArgs a) {
     for (int s = 0; s < NS; ++s) b[s] = ok ? *(const dbf16x8*)(q + 8 * s) : (dbf16x8){};
   }
 
-  // K tile t -> LDS (direct loads, XOR swizzle of 16-byte parts as the fused scan);
-  // rows past Lk load the last key, their scores are masked
-  auto issue_k = [&](int64_t t, unsigned char* dst) {
+  // tile t of K (16-byte parts XOR-swizzled by row, as in the fused scan) and of V (as it
+  // lies in memory); rows past Lk load the last key, their scores are masked
+  auto issue = [&](int64_t t, unsigned char* kd, unsigned char* vd) {
+    const int left = (int)(a.Lk - t * DN_KT < DN_KT ? a.Lk - t * DN_KT : DN_KT) - 1;
+    const uint16_t* kt = Kh + t * DN_KT * D;
+    const uint16_t* vt = Vh + t * DN_KT * D;
 #pragma unroll
     for (int j = 0; j < LPW; ++j) {
-      const int cidx = (wave * LPW + j) * 64 + tid % 64, r = cidx / CH, p = (cidx % CH) ^ (r & 7);
-      int64_t key = t * DN_KT + r;
-      key = key < a.Lk ? key : a.Lk - 1;
-      __builtin_amdgcn_global_load_lds((const void*)(Kh + key * D + p * 8),
-                                       (__attribute__((address_space(3))) void*)&dst[(wave * LPW + j) * 1024], 16,
-                                       0, 0);
-    }
-  };
-  // V tile t -> registers (thread: key tid % 64, feature groups of 8)
-  uint4 vreg[VLD];
-  auto load_v = [&](int64_t t) {
-    const int j = tid & 63;
-    int64_t key = t * DN_KT + j;
-    key = key < a.Lk ? key : a.Lk - 1;
-#pragma unroll
-    for (int e = 0; e < VLD; ++e) {
-      const int f0 = ((tid >> 6) + 4 * e) * 8;
-      vreg[e] = *(const uint4*)(Vh + key * D + f0);
-    }
-  };
-  auto store_vt = [&](uint16_t* vt) {
-    const int j = tid & 63;
-#pragma unroll
-    for (int e = 0; e < VLD; ++e) {
-      const int f0 = ((tid >> 6) + 4 * e) * 8;
-      const uint32_t w[4] = {vreg[e].x, vreg[e].y, vreg[e].z, vreg[e].w};
-#pragma unroll
-      for (int i = 0; i < 8; ++i) vt[vt_pos(f0 + i, j)] = (uint16_t)(w[i >> 1] >> (16 * (i & 1)));
+      const int cidx = (wave * LPW + j) * 64 + lane, r = cidx / CH, rr = min(r, left);
+      __builtin_amdgcn_global_load_lds((const void*)(kt + (uint32_t)(rr * D + ((cidx % CH) ^ (r & 7)) * 8)),
+                                       (__attribute__((address_space(3))) void*)&kd[(wave * LPW + j) * 1024], 16, 0, 0);
+      __builtin_amdgcn_global_load_lds((const void*)(vt + (uint32_t)(rr * D + (cidx % CH) * 8)),
+                                       (__attribute__((address_space(3))) void*)&vd[(wave * LPW + j) * 1024], 16, 0, 0);
     }
   };
 
@@ -126,7 +112,7 @@ __global__ __launch_bounds__(256, 2) void k_dense_attn(DenseArgs a) {
   float m_run = -INFINITY, l_run = 0.f;
   const float cexp = a.scale_log2e;
 
-  // scores of the 32-key block rb of tile t for the lane's query
+  // scores of the 32-key block rb of the tile for the lane's query
   auto block_scores = [&](const unsigned char* kb, int rb) {
     const int r = rb * 32 + n;
     dbf16x8 av[NS];
@@ -144,106 +130,91 @@ __global__ __launch_bounds__(256, 2) void k_dense_attn(DenseArgs a) {
       if (j >= a.Lk || (CAUSAL && j > qi)) acc[v] = -INFINITY;
     }
   };
-  auto tile = [&](int64_t t, const unsigned char* kb, const uint16_t* vt) {
+  auto tile = [&](int64_t t, const unsigned char* kb, const unsigned char* vb) {
     df32x16 s[2];
 #pragma unroll
-    for (int rb = 0; rb < 2; ++rb) {
-      s[rb] = block_scores(kb, rb);
-      const int64_t jb = t * DN_KT + rb * 32 + 4 * half;
-      if (t * DN_KT + DN_KT > a.Lk || (CAUSAL && t * DN_KT + DN_KT - 1 > q_first + wave * DN_QW)) mask(s[rb], jb);
+    for (int rb = 0; rb < 2; ++rb) s[rb] = block_scores(kb, rb);
+    if (t * DN_KT + DN_KT > a.Lk || (CAUSAL && t * DN_KT + DN_KT - 1 > q_first + wave * DN_QW)) {
+      mask(s[0], t * DN_KT + 4 * half);
+      mask(s[1], t * DN_KT + 32 + 4 * half);
     }
-    // running maximum of the query (both of its lanes)
-    float mt = s[0][0];
+    // the tile's maximum of the query (both of its lanes)
+    float mt = __builtin_elementwise_maximum(s[0][0], s[1][0]);
 #pragma unroll
-    for (int rb = 0; rb < 2; ++rb)
+    for (int v = 1; v < 16; ++v) mt = __builtin_elementwise_maximum(mt, __builtin_elementwise_maximum(s[0][v], s[1][v]));
+    mt = __builtin_elementwise_maximum(mt, __shfl_xor(mt, 32, 64));
+    // (not <=: for NaN too; queries whose maximum stays multiply by 1)
+    if (__builtin_amdgcn_ballot_w64(!(mt <= m_run))) {
+      const float m_new = fmaxf(m_run, mt);
+      const float alpha = m_new == -INFINITY ? 1.f : __builtin_amdgcn_exp2f((m_run - m_new) * cexp);  // m_run = -inf -> 0
+      m_run = m_new;
+      l_run *= alpha;
 #pragma unroll
-      for (int v = 0; v < 16; ++v) mt = fmaxf(mt, s[rb][v]);
-    mt = fmaxf(mt, __shfl_xor(mt, 32, 64));
-    const float m_new = fmaxf(m_run, mt);
-    const float m_use = m_new == -INFINITY ? 0.f : m_new;  // all keys masked so far: weights stay 0
-    const float alpha = exp2f((m_run - m_use) * cexp);     // m_run = -inf -> 0
-    m_run = m_new;
-    l_run *= alpha;
+      for (int db = 0; db < NDB; ++db)
 #pragma unroll
-    for (int db = 0; db < NDB; ++db)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) o[db][v] *= alpha;
-    const float off = m_use * cexp;
+        for (int v = 0; v < 16; ++v) o[db][v] *= alpha;
+    }
+    const float off = m_run == -INFINITY ? 0.f : m_run * cexp;  // all keys masked so far: weights stay 0
 #pragma unroll
     for (int rb = 0; rb < 2; ++rb) {
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {  // the weights replace the scores
-        s[rb][v] = exp2f(fmaf(s[rb][v], cexp, -off));
-        l_run += s[rb][v];
-      }
 #pragma unroll
       for (int st = 0; st < 2; ++st) {
         // B: the lane's 8 weights of keys 16 st + {4h..4h+3, 8+4h..8+4h+3} of the block
         dbf16x8 pb;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) pb[e] = (__bf16)s[rb][8 * st + e];
-        const int k0 = rb * 32 + 16 * st + 4 * half;  // first key of each 4-key group
+        for (int e = 0; e < 8; ++e) {
+          const float w = __builtin_amdgcn_exp2f(fmaf(s[rb][8 * st + e], cexp, -off));  // below 2^-126 it is 0
+          l_run += w;
+          pb[e] = (__bf16)w;
+        }
+        // A: rows 32 rb + 16 st + the same keys of V, columns n * NDB ..
+        uint32_t vr[8][VW];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const int key = rb * 32 + 16 * st + (e & 4) * 2 + 4 * half + (e & 3);
+          __builtin_memcpy(vr[e], __builtin_assume_aligned(vb + key * 2 * D + n * NDB * 2, 4 * VW), 4 * VW);
+        }
 #pragma unroll
         for (int db = 0; db < NDB; ++db) {
-          const int f = db * 32 + n;  // A row: output feature
-          const dbf16x4 lo = *(const dbf16x4*)(vt + vt_pos(f, k0));
-          const dbf16x4 hi = *(const dbf16x4*)(vt + vt_pos(f, k0 + 8));
-          const dbf16x8 av = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-          o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, pb, o[db], 0, 0, 0);
+          const uint32_t sel = db & 1 ? 0x07060302u : 0x05040100u;
+          const int w = db / 2;
+          const uint4 av = make_uint4(__builtin_amdgcn_perm(vr[1][w], vr[0][w], sel), __builtin_amdgcn_perm(vr[3][w], vr[2][w], sel),
+                                      __builtin_amdgcn_perm(vr[5][w], vr[4][w], sel), __builtin_amdgcn_perm(vr[7][w], vr[6][w], sel));
+          o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(dbf16x8, av), pb, o[db], 0, 0, 0);
         }
       }
     }
   };
 
-  // Pipeline, one tile of lookahead: during tile t the loads of K tile t+1 (direct to
-  // LDS) and of V tile t+2 (to registers) are in flight; V tile t+1 was written to
-  // V^T LDS at the start of tile t. Loads are issued V first, then K, so that the
-  // K tile can be awaited without waiting for the younger V loads.
-  if (ntiles > 0) {
-    load_v(0);
-    issue_k(0, ks0);
-    __builtin_amdgcn_s_waitcnt(DENSE_WAIT_VM(LPW));  // V tile 0 is in registers
-    store_vt(vt0);
-    if (ntiles > 1) load_v(1);
-  }
+  // One tile of lookahead: before tile t is read, this wave's loads of it are complete and
+  // the barrier publishes every wave's part; it also proves that no wave still reads the
+  // buffers the next loads overwrite. The buffers are named at compile time, so that reads
+  // of one pair do not wait for the loads into the other.
+  if (ntiles > 0) issue(0, ks0, vs0);
   for (int64_t t = 0; t < ntiles; t += 2) {
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int64_t tt = t + u;
-      if (tt >= ntiles) break;
-      const unsigned char* kcur = u ? ks1 : ks0;
-      unsigned char* knxt = u ? ks0 : ks1;
-      const uint16_t* vcur = u ? vt1 : vt0;
-      uint16_t* vnxt = u ? vt0 : vt1;
-      // in flight: K tile tt, then V tile tt+1 (if any); wait for K tile tt
-      if (tt + 1 < ntiles) __builtin_amdgcn_s_waitcnt(DENSE_WAIT_VM(VLD));
-      else __builtin_amdgcn_s_waitcnt(DENSE_WAIT_VM(0));
-      // publishes every wave's K tile tt parts and V^T tile tt stores, and ends every
-      // wave's reads of tile tt-1, whose buffers are refilled below
-      __syncthreads();
-      if (tt + 1 < ntiles) {
-        __builtin_amdgcn_s_waitcnt(DENSE_WAIT_VM(0));  // V tile tt+1 is in registers
-        store_vt(vnxt);
-        if (tt + 2 < ntiles) load_v(tt + 2);
-        issue_k(tt + 1, knxt);
-      }
-      tile(tt, kcur, vcur);
-    }
+    __builtin_amdgcn_s_waitcnt(DENSE_WAIT_VM0);
+    __syncthreads();
+    if (t + 1 < ntiles) issue(t + 1, ks1, vs1);
+    tile(t, ks0, vs0);
+    if (t + 1 >= ntiles) break;
+    __builtin_amdgcn_s_waitcnt(DENSE_WAIT_VM0);
+    __syncthreads();
+    if (t + 2 < ntiles) issue(t + 2, ks0, vs0);
+    tile(t + 1, ks1, vs1);
   }
   if (!ok) return;
   const float l = l_run + __shfl_xor(l_run, 32, 64);
   const float inv = l > 0.f ? 1.f / l : 0.f;
   uint16_t* dst = a.out + (bh * a.Lq + qi) * D;
 #pragma unroll
-  for (int db = 0; db < NDB; ++db)
+  for (int g = 0; g < 4; ++g) {
+    // rows 8 g + 4 h .. + 3 of every block: features (8 g + 4 h) * NDB .. of the lane's query
+    dbf16x4 w[NDB];
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      // features db*32 + 8g + 4h .. +3 of the lane's query
-      dbf16x4 w;
+    for (int e = 0; e < 4 * NDB; ++e) w[e / 4][e % 4] = (__bf16)(o[e % NDB][4 * g + e / NDB] * inv);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) w[e] = (__bf16)(o[db][4 * g + e] * inv);
-      *(dbf16x4*)(dst + db * 32 + 8 * g + 4 * half) = w;
-    }
+    for (int q = 0; q < NDB; ++q) *(dbf16x4*)(dst + (8 * g + 4 * half) * NDB + 4 * q) = w[q];
+  }
 }
 
 hipError_t launch_dense(const Problem& pb, const Pass& ps, hipStream_t st) {
