@@ -21,7 +21,7 @@ import sys
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
-SOURCES = ["csrc/topk_kernels.hip", "csrc/topk_rows.hip", "csrc/topk_cells.hip",
+SOURCES = ["csrc/topk_kernels.hip", "csrc/topk_rows.hip", "csrc/topk_cells.hip", "csrc/topk_few.hip", "csrc/topk_keep.hip",
            "csrc/topk_dense.hip", "csrc/topk_api.hip"]
 LIB = os.path.join(PKG, "libtopk.so")
 LIB_CHECK = os.path.join(PKG, "libtopk_check.so")

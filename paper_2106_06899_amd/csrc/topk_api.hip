@@ -240,6 +240,7 @@ size_t plan_total(const Plan& pl, const Problem& pb) {
 PassBufs carve(const Problem& pb, const Plan& pl, char* ws) {
   const size_t rows = (size_t)pl.per_pass * pb.C;
   PassBufs b = {};
+  b.sel_sorted = 1;
   size_t off = 0;
   b.redo_count = (int32_t*)(ws + off);
   off += ALIGN;
@@ -265,6 +266,10 @@ PassBufs carve(const Problem& pb, const Plan& pl, char* ws) {
     // one list per row, which the fused scan and the filtered tile GEMM append to; the
     // filtered path's scan keeps one list per row and half-wave
     b.cand_single = pl.path == PATH_FILTER && filter_scan_ok(pb) ? 0 : 1;
+    // the filtered path's scan appends each list in key order, which the sums can follow; the
+    // other lists' order depends on scheduling, and up to 64 keys are sorted as quickly (16
+    // heads of 3000, k = 20: 37 us either way; with the cache outputs, k = 40, 2151: 55 / 58)
+    b.sel_sorted = b.cand_single || pb.k <= 64;
     if (pl.path == PATH_FILTER) {
       b.samp = (float*)(ws + off);
       off += up(rows * (size_t)((pb.Lk + FILTER_KSTRIDE - 1) / FILTER_KSTRIDE) * 4 + FILTER_SAMP_PAD);

@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace topk {
 
 typedef __bf16 bf16x8 __attribute__((__vector_size__(16)));
@@ -88,6 +90,18 @@ __device__ __forceinline__ uint32_t wave_extreme_u32_full(uint32_t x) {
   const uint32_t r0 = (uint32_t)__builtin_amdgcn_readlane((int)x, 0), r1 = (uint32_t)__builtin_amdgcn_readlane((int)x, 16);
   const uint32_t r2 = (uint32_t)__builtin_amdgcn_readlane((int)x, 32), r3 = (uint32_t)__builtin_amdgcn_readlane((int)x, 48);
   return op(op(r0, r1), op(r2, r3));
+}
+// The same of floats (NaN if any is).
+template <bool MAX>
+__device__ __forceinline__ float wave_extreme_f32_full(float x) {
+  auto op = [](float u, float v) { return MAX ? __builtin_elementwise_maximum(u, v) : __builtin_elementwise_minimum(u, v); };
+  auto dpp = [](float v, auto ctrl) { return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), decltype(ctrl)::value, 0xF, 0xF, false)); };
+  x = op(x, dpp(x, std::integral_constant<int, 0xB1>{}));   // quad [1,0,3,2]
+  x = op(x, dpp(x, std::integral_constant<int, 0x4E>{}));   // quad [2,3,0,1]
+  x = op(x, dpp(x, std::integral_constant<int, 0x141>{}));  // row_half_mirror
+  x = op(x, dpp(x, std::integral_constant<int, 0x140>{}));  // row_mirror
+  auto at = [&](int l) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), l)); };
+  return op(op(at(0), at(16)), op(at(32), at(48)));
 }
 // Inclusive prefix sum over the 64 lanes of a wave whose lanes are all active, by
 // DPP: row shifts 1, 2, 4, 8 scan each row of 16 lanes, then the broadcasts of lane

@@ -64,7 +64,8 @@ inline bool filter_scan_ok(const Problem& pb) { return pb.dtype == T_BF16 && pb.
 
 // Workspace pointers of one pass.
 struct PassBufs {
-  uint64_t* sel;      // [rows, k] selected keys, (score desc, index asc); 0 pads
+  uint64_t* sel;      // [rows, k] selected keys, 0 pads
+  int sel_sorted;     // sel in (score desc, index asc) order; 0: in the order of the candidate lists
   int32_t* redo_list; // [rows]
   int32_t* redo_count;
   float* scores;      // chunk-tile path: [rows, Lk]; fused path: redo rows [REDO_CAP + REDO_BLOCKS, Lk]
@@ -110,6 +111,8 @@ constexpr int64_t FEW_ROWS = 128;
 __host__ __device__ inline int64_t few_row_len(int64_t Lk) { return (Lk + 15) / 16 * 16; }
 hipError_t launch_few_scores(const Problem& pb, const Pass& ps, const PassBufs& b, hipStream_t st);
 hipError_t launch_few_select(const Problem& pb, const Pass& ps, const PassBufs& b, hipStream_t st);
+// the multi-pass select of the rows on the redo list, from score rows of row_len
+hipError_t launch_tile_redo(const Problem& pb, const Pass& ps, const PassBufs& b, int64_t row_len, hipStream_t st);
 
 hipError_t launch_init(const PassBufs& b, hipStream_t st);
 hipError_t launch_tile_scores(const Problem& pb, const Pass& ps, const PassBufs& b, hipStream_t st);
@@ -117,6 +120,7 @@ hipError_t launch_tile_select(const Problem& pb, const Pass& ps, const PassBufs&
 hipError_t launch_fused_scan(const Problem& pb, const Pass& ps, const PassBufs& b, const ScanCfg& cfg,
                              hipStream_t st);
 hipError_t launch_cand_select(const Problem& pb, const Pass& ps, const PassBufs& b, hipStream_t st);
+hipError_t launch_keep_select(const Problem& pb, const Pass& ps, const PassBufs& b, hipStream_t st);
 hipError_t launch_redo(const Problem& pb, const Pass& ps, const PassBufs& b, hipStream_t st);
 hipError_t launch_finalize(const Problem& pb, const Pass& ps, const PassBufs& b, hipStream_t st);
 hipError_t launch_mfma_probe(int32_t* rows, int32_t* cols, hipStream_t st);

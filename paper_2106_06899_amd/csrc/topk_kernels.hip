@@ -15,8 +15,7 @@
 // Selected keys are 64-bit words  (ord(score) << 32) | (0xFFFFFFFF - index)  so
 // that one unsigned comparison implements the total order (score desc, index
 // asc) used for ties; ord() maps fp32 to an order-preserving u32, with -0 == +0.
-#include "topk_device.h"
-#include "topk_internal.h"
+#include "topk_select.h"
 
 #include <math.h>
 
@@ -29,161 +28,6 @@ typedef float f32x16 __attribute__((__vector_size__(64)));
 // s_waitcnt immediate that waits until at most n vector-memory operations are
 // outstanding and does not wait on the other counters
 #define TOPK_WAIT_VM(n) (((n) & 15) | (7 << 4) | (15 << 8) | (((n) >> 4) << 14))
-
-// Pass-local row -> (head, query index); false for padding rows of a partial chunk.
-struct RowRef {
-  int64_t bh, i;
-  bool ok;
-};
-__device__ __forceinline__ RowRef row_of(const Problem& pb, const Pass& ps, int64_t p) {
-  int64_t chunk_local, r, id, c;
-  RowRef rr;
-  if (((uint64_t)p | (uint64_t)pb.C | (uint64_t)(ps.c0 + ps.nc) | (uint64_t)ps.nchunk) >> 31 == 0) {
-    // the common case: 32-bit divisions (a few instructions instead of a 64-bit routine)
-    const uint32_t cl32 = (uint32_t)p / (uint32_t)pb.C, id32 = (uint32_t)ps.c0 + cl32;
-    chunk_local = cl32;
-    r = (uint32_t)p - cl32 * (uint32_t)pb.C;
-    id = id32;
-    rr.bh = id32 / (uint32_t)ps.nchunk;
-    c = id32 - (uint32_t)rr.bh * (uint32_t)ps.nchunk;
-  } else {
-    chunk_local = p / pb.C;
-    r = p - chunk_local * pb.C;
-    id = ps.c0 + chunk_local;
-    rr.bh = id / ps.nchunk;
-    c = id - rr.bh * ps.nchunk;
-  }
-  rr.i = pb.q0 + c * pb.C + r;
-  rr.ok = chunk_local < ps.nc && rr.i < pb.q1;
-  return rr;
-}
-__device__ __forceinline__ int64_t valid_keys(const Problem& pb, int64_t i) {
-  return pb.causal ? (i + 1 < pb.Lk ? i + 1 : pb.Lk) : pb.Lk;
-}
-
-// ------------------------------------------------------------------ team primitives
-// A "team" is one workgroup of NT threads (NT = 64 or 256); all sync is __syncthreads.
-template <int NT>
-__device__ __forceinline__ uint32_t team_excl_scan(uint32_t x, uint32_t* tmp) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  uint32_t incl = x;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    uint32_t y = __shfl_up(incl, off, 64);
-    if (lane >= off) incl += y;
-  }
-  if (NT == 64) return incl - x;
-  if (lane == 63) tmp[w] = incl;
-  __syncthreads();
-  uint32_t base = 0;
-  for (int q = 0; q < w; ++q) base += tmp[q];
-  __syncthreads();
-  return base + incl - x;
-}
-
-// Digits a sampled threshold resolves: the sign, the exponent and the top 7 bits of the
-// mantissa of the R-th largest sample (finer resolution only trims a few candidates).
-constexpr int THRESH_PASSES = 2;
-
-// Exact radix select of the k_eff largest keys among n (distinct) 64-bit keys,
-// 8 bits per pass from the top. On return the selected set is exactly
-// { key : (key >> shift) >= (prefix >> shift) }. With max_passes < 8 it stops early
-// and the set holds the k_eff largest keys and possibly more (the rest of the last
-// digit's bucket), which is all a threshold needs.
-template <int NT, class GetKey>
-__device__ void team_radix_select(const GetKey& getkey, int64_t n, uint32_t k_eff, uint32_t* hist,
-                                  uint32_t* misc, int* shift_out, uint64_t* prefix_out, int max_passes = 8) {
-  uint64_t prefix = 0;
-  int shift = 64;
-  uint32_t kr = k_eff;
-  for (int pass = 0; pass < max_passes; ++pass) {
-    shift -= 8;
-    for (int b = threadIdx.x; b < 256; b += NT) hist[b] = 0;
-    __syncthreads();
-    for (int64_t e = threadIdx.x; e < n; e += NT) {
-      const uint64_t key = getkey(e);
-      const bool match = pass == 0 || (key >> (shift + 8)) == (prefix >> (shift + 8));
-      if (match) atomicAdd(&hist[(uint32_t)(key >> shift) & 255u], 1u);
-    }
-    __syncthreads();
-    constexpr int BPT = 256 / NT;
-    uint32_t c[BPT];
-    uint32_t local = 0;
-#pragma unroll
-    for (int e = 0; e < BPT; ++e) {
-      c[e] = hist[255 - (threadIdx.x * BPT + e)];  // bins in descending digit order
-      local += c[e];
-    }
-    uint32_t run = team_excl_scan<NT>(local, misc);
-#pragma unroll
-    for (int e = 0; e < BPT; ++e) {
-      if (run < kr && kr <= run + c[e]) {
-        misc[4] = 255u - (uint32_t)(threadIdx.x * BPT + e);
-        misc[5] = run;
-        misc[6] = c[e];
-      }
-      run += c[e];
-    }
-    __syncthreads();
-    const uint32_t digit = misc[4], above = misc[5], cnt = misc[6];
-    __syncthreads();
-    prefix |= (uint64_t)digit << shift;
-    kr -= above;
-    if (cnt == kr) break;  // every key of this bucket is selected
-  }
-  *shift_out = shift;
-  *prefix_out = prefix;
-}
-
-// Bitonic sort of P (power of two) keys in LDS, descending.
-template <int NT>
-__device__ void team_sort_desc(uint64_t* s, int P) {
-  for (int size = 2; size <= P; size <<= 1) {
-    for (int stride = size >> 1; stride > 0; stride >>= 1) {
-      for (int t = threadIdx.x; t < (P >> 1); t += NT) {
-        const int i = 2 * stride * (t / stride) + (t % stride);
-        const int j = i + stride;
-        const bool desc = (i & size) == 0;
-        const uint64_t a = s[i], b = s[j];
-        if ((a < b) == desc) {
-          s[i] = b;
-          s[j] = a;
-        }
-      }
-      __syncthreads();
-    }
-  }
-}
-
-// Select the k_eff largest of n keys, sort them and write k words to out (0 pads).
-// sbuf holds P >= k_eff keys (power of two).
-template <int NT, class GetKey>
-__device__ void team_topk(const GetKey& getkey, int64_t n, uint32_t k_eff, uint32_t k, uint64_t* sbuf, int P,
-                          uint32_t* hist, uint32_t* misc, uint64_t* out) {
-  int shift;
-  uint64_t prefix;
-  team_radix_select<NT>(getkey, n, k_eff, hist, misc, &shift, &prefix);
-  const uint64_t lim = prefix >> shift;
-  if (threadIdx.x == 0) misc[7] = 0;
-  for (int t = threadIdx.x; t < P; t += NT) sbuf[t] = 0;
-  __syncthreads();
-  for (int64_t e = threadIdx.x; e < n; e += NT) {
-    const uint64_t key = getkey(e);
-    if ((key >> shift) >= lim) {
-      const uint32_t pos = atomicAdd(&misc[7], 1u);
-      if (pos < (uint32_t)P) sbuf[pos] = key;
-    }
-  }
-  __syncthreads();
-  team_sort_desc<NT>(sbuf, P);
-  for (uint32_t t = threadIdx.x; t < k; t += NT) out[t] = t < k_eff ? sbuf[t] : 0ull;
-}
-
-__host__ __device__ __forceinline__ int pow2_at_least(int64_t x) {
-  int p = 1;
-  while (p < x) p <<= 1;
-  return p;
-}
 
 // ------------------------------------------------------------------ init
 __global__ void k_init(int32_t* redo_count) {
@@ -529,10 +373,6 @@ __global__ __launch_bounds__(256, 2) void k_tile_scores_mfma(Problem pb, Pass ps
 // testing them; rows must start 16-byte aligned when vec.
 // (The gathered set {score >= ts} holds the row's top k whenever it holds k keys:
 // a key outside it is below every key inside.)
-__device__ __forceinline__ uint64_t raw_to_key(uint64_t w) {
-  return ((uint64_t)ord_u32(__uint_as_float((uint32_t)(w >> 32))) << 32) | (w & 0xFFFFFFFFull);
-}
-
 template <class Reserve>
 __device__ __forceinline__ void gather_row(const float* row, int64_t nv, float ts, bool vec, int64_t lane0,
                                            int64_t lanes, uint64_t* cbuf, uint32_t cap, const Reserve& reserve) {
@@ -1247,153 +1087,7 @@ __global__ __launch_bounds__(256, D == 64 ? (CAUSAL ? ScanShape<G>::OCC_CAUSAL :
 //    broadcast with ballot/shuffle, only the histogram lives in LDS;
 //  * the selected keys are compacted with mbcnt and sorted (descending) by a
 //    bitonic network on registers, E = P/64 keys per lane.
-constexpr int CAND_REGS = 16;
 
-template <int E>
-__device__ __forceinline__ void wave_sort_store(const uint64_t* sbuf, uint32_t k_eff, int64_t k, uint64_t* out) {
-  const int lane = threadIdx.x & 63;
-  uint64_t r[E];
-#pragma unroll
-  for (int e = 0; e < E; ++e) r[e] = (uint32_t)(e * 64 + lane) < k_eff ? sbuf[e * 64 + lane] : 0ull;
-  wave_sort_desc<E>(r);
-#pragma unroll
-  for (int e = 0; e < E; ++e)
-    if (e * 64 + lane < k) out[e * 64 + lane] = r[e];
-}
-
-// Radix select on n <= E * 64 distinct keys held in registers (key[e] is element
-// e*64 + lane; elements >= n are ignored). Returns (shift, prefix): the k_eff
-// largest keys are exactly those with (key >> shift) >= (prefix >> shift). One
-// wave runs it (hist: 256 words of LDS of its own); it synchronises only itself.
-// With max_passes, the select stops after that many digits: the set then holds the
-// k_eff largest keys and possibly more (the rest of the last digit's bucket), which
-// is all a threshold needs.
-template <int E>
-__device__ __forceinline__ void wave_radix_select(const uint64_t (&key)[E], int n, uint32_t k_eff, uint32_t* hist,
-                                                  int* shift_out, uint64_t* prefix_out, int max_passes = 8) {
-  const int lane = threadIdx.x & 63;
-  uint64_t kmin = ~0ull, kmax = 0ull;
-#pragma unroll
-  for (int e = 0; e < E; ++e) {
-    if (lane + 64 * e < n) {
-      kmin = key[e] < kmin ? key[e] : kmin;
-      kmax = key[e] > kmax ? key[e] : kmax;
-    }
-  }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    const uint64_t a0 = xor_lane_u64(kmin, off), a1 = xor_lane_u64(kmax, off);
-    kmin = a0 < kmin ? a0 : kmin;
-    kmax = a1 > kmax ? a1 : kmax;
-  }
-  // bits above the highest differing bit are common to every candidate; the first
-  // digit starts at that bit (not at a byte boundary), so it splits the candidates
-  // over as many bins as 8 bits can (scores above a threshold often share their top
-  // byte, which would pile a byte-aligned first pass onto a few bins)
-  const uint64_t diff = kmin ^ kmax;
-  int shift = diff == 0 ? 1 : 64 - __builtin_clzll(diff);  // bits [0, shift) differ
-  uint64_t prefix = (shift >= 64) ? 0 : (kmax >> shift) << shift;
-  uint32_t kr = k_eff;
-  for (int pass = 0; pass < max_passes && shift > 0 && kr < (uint32_t)n; ++pass) {
-    const int top = shift;  // keys still in play share every bit at or above top
-    const int width = top < 8 ? top : 8;
-    shift = top - width;
-    reinterpret_cast<uint4*>(hist)[lane] = make_uint4(0u, 0u, 0u, 0u);
-    wave_sync_lds();
-    const uint64_t pre_hi = top >= 64 ? 0 : prefix >> top;
-    const uint32_t dmask = (1u << width) - 1u;
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      const bool match = lane + 64 * e < n && (top >= 64 || (key[e] >> top) == pre_hi);
-      if (match) atomicAdd(&hist[(uint32_t)(key[e] >> shift) & dmask], 1u);
-    }
-    wave_sync_lds();
-    const uint4 h4 = reinterpret_cast<const uint4*>(hist)[63 - lane];  // bins 255-4l .. 252-4l
-    const uint32_t c4[4] = {h4.w, h4.z, h4.y, h4.x};                   // descending digit order
-    const uint32_t local = c4[0] + c4[1] + c4[2] + c4[3];
-    uint32_t run = wave_incl_scan_full(local) - local;
-    uint32_t digit = 0, above = 0, cnt = 0;
-    bool here = false;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      if (!here && run < kr && kr <= run + c4[e]) {
-        here = true;
-        digit = 255u - (uint32_t)(lane * 4 + e);
-        above = run;
-        cnt = c4[e];
-      }
-      run += c4[e];
-    }
-    const uint64_t who = __ballot(here);
-    const int src = __builtin_ctzll(who);  // wave-uniform
-    digit = (uint32_t)__builtin_amdgcn_readlane((int)digit, src);
-    above = (uint32_t)__builtin_amdgcn_readlane((int)above, src);
-    cnt = (uint32_t)__builtin_amdgcn_readlane((int)cnt, src);
-    wave_sync_lds();  // hist is cleared again by the next pass
-    prefix |= (uint64_t)digit << shift;
-    kr -= above;
-    if (cnt == kr) break;  // every key of this bucket is selected
-  }
-  *shift_out = shift;
-  *prefix_out = prefix;
-}
-
-// The k_eff <= 64 * E distinct keys of sbuf, stored in descending order (the first
-// 64 * E of k words, 0 pads): each key goes to its rank, the number of larger keys,
-// counted against every key through broadcast LDS reads. Two VALU per comparison:
-// at E = 1 faster than the bitonic network (measured slower at E = 2).
-template <int E>
-__device__ __forceinline__ void wave_rank_store(const uint64_t* sbuf, uint32_t k_eff, int64_t k, uint64_t* out) {
-  const int lane = threadIdx.x & 63;
-  uint64_t x[E];
-  uint32_t rank[E];
-#pragma unroll
-  for (int e = 0; e < E; ++e) {
-    x[e] = (uint32_t)(e * 64 + lane) < k_eff ? sbuf[e * 64 + lane] : 0ull;
-    rank[e] = 0;
-  }
-#pragma unroll 8
-  for (uint32_t j = 0; j < k_eff; ++j) {
-    const uint64_t y = sbuf[j];
-#pragma unroll
-    for (int e = 0; e < E; ++e) rank[e] += y > x[e] ? 1u : 0u;
-  }
-#pragma unroll
-  for (int e = 0; e < E; ++e) {
-    const int t = e * 64 + lane;
-    if ((uint32_t)t < k_eff) out[rank[e]] = x[e];
-    else if (t < k) out[t] = 0ull;
-  }
-}
-
-// The k_eff (<= KCAP: 256 or 512) largest of n <= E * 64 register keys, sorted
-// descending, written as k words to out (0 pads). sbuf: KCAP keys of LDS.
-template <int E, int KCAP = 256>
-__device__ __forceinline__ void wave_select_store(const uint64_t (&key)[E], int n, uint32_t k_eff, int64_t k,
-                                                  uint64_t* sbuf, uint32_t* hist, uint64_t* out) {
-  const int lane = threadIdx.x & 63;
-  int shift;
-  uint64_t prefix;
-  wave_radix_select<E>(key, n, k_eff, hist, &shift, &prefix);
-  // selected: (key >> shift) >= (prefix >> shift); compact them into sbuf
-  const uint64_t lim = prefix >> shift;
-  int base = 0;
-#pragma unroll
-  for (int e = 0; e < E; ++e) {
-    const bool take = lane + 64 * e < n && (key[e] >> shift) >= lim;
-    const uint64_t m = __ballot(take);
-    const int pos = base + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-    if (take && pos < KCAP) sbuf[pos] = key[e];
-    base += __popcll(m);
-  }
-  wave_sync_lds();
-  int sorted;
-  if (k_eff <= 64) wave_rank_store<1>(sbuf, k_eff, k, out), sorted = 64;
-  else if (k_eff <= 128) wave_sort_store<2>(sbuf, k_eff, k, out), sorted = 128;
-  else if (KCAP <= 256 || k_eff <= 256) wave_sort_store<4>(sbuf, k_eff, k, out), sorted = 256;
-  else wave_sort_store<(KCAP > 256 ? 8 : 4)>(sbuf, k_eff, k, out), sorted = 512;
-  for (int64_t t = lane + sorted; t < k; t += 64) out[t] = 0ull;
-}
 
 // Reads a row's n candidate words (c0 from b0, the rest from b1) into E registers
 // per lane as order-preserving keys, then selects and stores.
@@ -1728,236 +1422,6 @@ __global__ __launch_bounds__(256) void k_tile_select_redo(Problem pb, Pass ps, c
   }
 }
 
-// ------------------------------------------------------------------ few queries
-// Heads of at most FEW_ROWS queries (bf16): the scan and the filtered GEMM walk all of a
-// head's keys in workgroups made for 128 to 256 queries, a handful of workgroups that use a
-// few of their lanes. Here the keys are spread instead: one wave scores 64 keys against up
-// to 64 queries (16 x 16 blocks, operands straight from global memory), writes the scores
-// and the maximum of every 16 keys (as an order-preserving key). The k-th largest of a
-// row's maxima is a bound below which no top-k score lies, since k blocks hold one at or
-// above it; the select reads the maxima, then only the blocks that reach the bound (a little
-// over k of them).
-// Scores: bound by reading the keys once (64 heads of 20001 keys, d = 128, 5 queries: 328 MB
-// and 25 MB of scores in 78 us, 4.5 TB/s; the scan took 408), with more queries by writing
-// the scores. Select: latency, 20 us a row whatever the number of rows up to a few thousand.
-typedef float f32x4 __attribute__((__vector_size__(16)));
-
-template <int RT, int KT>
-__global__ __launch_bounds__(256, RT <= 2 ? 4 : 2) void k_few_scores(Problem pb, Pass ps, PassBufs bufs) {
-  constexpr int NS = 16 / KT;  // 32-feature steps whose keys are in flight together
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n = lane & 15, g = lane >> 4;
-  if (blockIdx.x == 0 && threadIdx.x == 0) *bufs.redo_count = 0;  // for the select
-  // key ranges fastest (consecutive ones on one XCD), then groups of 16 RT queries, then heads
-  const int64_t NG = gridDim.x, bid = blockIdx.x;
-  int64_t wg = (NG % 8 == 0) ? (bid % 8) * (NG / 8) + bid / 8 : bid;
-  const int64_t nk = (pb.Lk + 64 * KT - 1) / (64 * KT), nq = (pb.Lq + 16 * RT - 1) / (16 * RT);
-  const int64_t key0 = (wg % nk) * (64 * KT) + wave * (16 * KT);
-  wg /= nk;
-  const int r0 = (int)(wg % nq) * 16 * RT;
-  const int64_t cl = wg / nq, bh = ps.c0 + cl;  // one chunk per head
-  if (key0 >= pb.Lk) return;
-  const uint16_t* Kh = (const uint16_t*)pb.K + bh * pb.kv_head_stride + key0 * pb.d;
-  const uint16_t* Qh = (const uint16_t*)pb.Q + bh * pb.Lq * pb.d;
-  const int d = (int)pb.d, left = (int)(pb.Lk - key0 < 16 * KT ? pb.Lk - key0 : 16 * KT), rows = (int)pb.Lq;
-  uint32_t ko[KT], qo[RT];
-#pragma unroll
-  for (int t = 0; t < KT; ++t) ko[t] = (uint32_t)(min(16 * t + n, left - 1) * d + 8 * g);  // past the end: the last key
-#pragma unroll
-  for (int r = 0; r < RT; ++r) qo[r] = (uint32_t)(min(r0 + 16 * r + n, rows - 1) * d + 8 * g);
-  f32x4 acc[KT][RT];
-#pragma unroll
-  for (int t = 0; t < KT; ++t)
-#pragma unroll
-    for (int r = 0; r < RT; ++r) acc[t][r] = (f32x4){};
-  // 32 features a step, lane group g taking 8 g .. 8 g + 7
-  for (int f0 = 0; f0 < d; f0 += 32 * NS) {
-    bf16x8 kf[NS][KT];
-#pragma unroll
-    for (int s = 0; s < NS; ++s)
-      if (f0 + 32 * s < d)
-#pragma unroll
-        for (int t = 0; t < KT; ++t) kf[s][t] = *(const bf16x8*)(Kh + ko[t] + f0 + 32 * s);
-#pragma unroll
-    for (int s = 0; s < NS; ++s)
-      if (f0 + 32 * s < d) {
-        bf16x8 qf[RT];
-#pragma unroll
-        for (int r = 0; r < RT; ++r) qf[r] = *(const bf16x8*)(Qh + qo[r] + f0 + 32 * s);
-#pragma unroll
-        for (int t = 0; t < KT; ++t)
-#pragma unroll
-          for (int r = 0; r < RT; ++r) acc[t][r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[s][t], qf[r], acc[t][r], 0, 0, 0);
-      }
-  }
-  // lane: query n of row block r, keys 4 g .. 4 g + 3 of key block t
-  const int64_t ld = few_row_len(pb.Lk), nb = ld / 16;
-#pragma unroll
-  for (int r = 0; r < RT; ++r) {
-    const int row = r0 + 16 * r + n;
-    const int64_t p = cl * pb.C + row;
-#pragma unroll
-    for (int t = 0; t < KT; ++t) {
-      uint32_t m = 0;
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (16 * t + 4 * g + u < left) m = max(m, ord_u32(acc[t][r][u]));
-      m = max(m, (uint32_t)__shfl_xor((int)m, 16, 64));
-      m = max(m, (uint32_t)__shfl_xor((int)m, 32, 64));
-      if (row < rows && 16 * t < left) {  // the row's last block is padded: its extra scores are never read as keys
-        *(f32x4*)(bufs.scores + p * ld + key0 + 16 * t + 4 * g) = acc[t][r];
-        if (g == 0) bufs.blk[p * nb + key0 / 16 + t] = m;
-      }
-    }
-  }
-}
-
-// One wave per row, 64 E >= blocks; rows whose bound lets too many blocks or scores
-// through (many equal scores) go to the redo list. CAP: candidates held, KCAP >= k.
-template <int E, int KCAP>
-__global__ __launch_bounds__(64) void k_few_select(Problem pb, Pass ps, PassBufs bufs) {
-  constexpr int CAP = 4 * KCAP;
-  __shared__ uint64_t cbuf[CAP];  // candidates; the final sort reuses its start
-  __shared__ uint32_t hist[256];
-  __shared__ uint16_t blist[CAP];
-  const int64_t p = blockIdx.x;
-  const RowRef rr = row_of(pb, ps, p);
-  if (!rr.ok) return;
-  const int lane = threadIdx.x & 63;
-  const int k = (int)pb.k, nb = (int)(few_row_len(pb.Lk) / 16);
-  const uint32_t* bm = bufs.blk + p * nb;
-  uint32_t u[E], mx = 0, mn = 0xFFFFFFFFu;
-#pragma unroll
-  for (int e = 0; e < E; ++e) u[e] = lane + 64 * e < nb ? bm[lane + 64 * e] : 0u;
-#pragma unroll
-  for (int e = 0; e < E; ++e) {
-    mx = max(mx, u[e]);
-    if (lane + 64 * e < nb) mn = min(mn, u[e]);
-  }
-  // a bound that k to k + k / 8 + 4 blocks reach (or, among equal maxima, more): halving by
-  // value, by key where that ends between two keys or after 24 steps
-  const uint32_t top = wave_extreme_u32_full<true>(mx);
-  uint32_t lo = wave_extreme_u32_full<false>(mn), hi = top + 1;
-  int clo = nb;
-  const int enough = k + k / 8 + 4;
-  for (int it = 0; clo > enough && hi - lo > 1; ++it) {
-    uint32_t t = lo + (hi - lo) / 2;
-    if (it < 24) {
-      const float fl = ord_to_f32(lo), fh = ord_to_f32(hi - 1);
-      const uint32_t v = (uint32_t)__builtin_amdgcn_readfirstlane((int)ord_u32(fmaf(fh - fl, 0.5f, fl)));
-      t = v > lo && v < hi ? v : t;
-    }
-    uint64_t ge[E];
-    int c = 0;
-#pragma unroll
-    for (int e = 0; e < E; ++e) ge[e] = __builtin_amdgcn_ballot_w64(u[e] >= t);
-#pragma unroll
-    for (int e = 0; e < E; ++e) c += (int)__popcll(ge[e]);
-    if (c >= k) {
-      lo = t;
-      clo = c;
-    } else {
-      hi = t;
-    }
-  }
-  bool redo = clo > CAP;
-  uint32_t c = 0;
-  if (!redo) {
-    int base = 0;
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      const uint64_t m = __builtin_amdgcn_ballot_w64(u[e] >= lo && lane + 64 * e < nb);
-      const int pos = base + (int)lanes_below(m);
-      if (u[e] >= lo && lane + 64 * e < nb) blist[pos] = (uint16_t)(lane + 64 * e);
-      base += (int)__popcll(m);
-    }
-    wave_sync_lds();
-    // 16 blocks at a time, four lanes a block; four such loads in flight
-    const float* row = bufs.scores + p * few_row_len(pb.Lk);
-    constexpr int U = 4;
-    for (int i0 = 0; i0 < clo; i0 += 16 * U) {
-      f32x4 x[U];
-      int key[U];
-#pragma unroll
-      for (int q = 0; q < U; ++q) {
-        const int i = i0 + 16 * q + (lane >> 2);
-        key[q] = 16 * (int)blist[i < clo ? i : 0] + 4 * (lane & 3);
-        x[q] = *(const f32x4*)(row + key[q]);
-        if (i >= clo) key[q] = 0x7FFFFFF0;
-      }
-#pragma unroll
-      for (int q = 0; q < U; ++q)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const bool in = key[q] + v < pb.Lk && ord_u32(x[q][v]) >= lo;
-          const uint64_t m = __builtin_amdgcn_ballot_w64(in);
-          const uint32_t pos = c + lanes_below(m);
-          if (in && pos < (uint32_t)CAP)
-            cbuf[pos] = ((uint64_t)__float_as_uint(x[q][v]) << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)(key[q] + v));
-          c += (uint32_t)__popcll(m);
-        }
-    }
-    redo = c > (uint32_t)CAP;
-  }
-  if (redo) {
-    if (lane == 0) bufs.redo_list[atomicAdd(bufs.redo_count, 1)] = (int32_t)p;
-    return;
-  }
-  uint64_t* out = bufs.sel + p * pb.k;
-  auto select = [&](auto tag) {
-    constexpr int F = decltype(tag)::value;
-    uint64_t key[F];
-#pragma unroll
-    for (int e = 0; e < F; ++e) key[e] = (uint32_t)(lane + 64 * e) < c ? raw_to_key(cbuf[lane + 64 * e]) : 0ull;
-    __syncthreads();  // the sort's buffer is the candidates' own
-    wave_select_store<F, KCAP>(key, (int)c, (uint32_t)k, k, cbuf, hist, out);
-  };
-  wave_sync_lds();
-  if (c <= 192) select(std::integral_constant<int, 3>{});
-  else if (c <= 384) select(std::integral_constant<int, 6>{});
-  else if (KCAP <= 256 || c <= 1024) select(std::integral_constant<int, 16>{});
-  else select(std::integral_constant<int, CAP / 64>{});
-}
-
-hipError_t launch_few_scores(const Problem& pb, const Pass& ps, const PassBufs& b, hipStream_t st) {
-  const int RT = pb.Lq <= 16 ? 1 : pb.Lq <= 32 ? 2 : 4;
-  const int64_t nq = (pb.Lq + 16 * RT - 1) / (16 * RT) * ps.nc;
-  // 64 keys a wave, or 16 (more of their features in flight) where that would leave fewer
-  // than two waves a CU: 24 tokens, d_model 768, d_ff 16384 (256 or 1024 waves) 24 -> 16 us;
-  // 8 tokens, 1024, 65536 (1024 or 4096 waves) 30 -> 33 us
-  const int KT = (pb.Lk + 63) / 64 * nq < 512 ? 1 : 4;
-  const int64_t g = ((pb.Lk + 64 * KT - 1) / (64 * KT)) * nq;
-  if (g > 0x7FFFFFFF || pb.dtype != T_BF16 || pb.d % 32 != 0 || ps.nchunk != 1 || pb.C < pb.Lq || !b.blk) return hipErrorInvalidValue;
-#define TOPK_FEW(RT_)                                                                 \
-  do {                                                                                \
-    if (KT == 1) k_few_scores<RT_, 1><<<(unsigned)g, 256, 0, st>>>(pb, ps, b);        \
-    else k_few_scores<RT_, 4><<<(unsigned)g, 256, 0, st>>>(pb, ps, b);                \
-  } while (0)
-  if (RT == 1) TOPK_FEW(1);
-  else if (RT == 2) TOPK_FEW(2);
-  else TOPK_FEW(4);
-#undef TOPK_FEW
-  return hipGetLastError();
-}
-
-hipError_t launch_few_select(const Problem& pb, const Pass& ps, const PassBufs& b, hipStream_t st) {
-  const int64_t nb = few_row_len(pb.Lk) / 16;
-  const unsigned g = (unsigned)(ps.nc * pb.C);
-  if (nb > 4096 || pb.k > 512) return hipErrorInvalidValue;
-#define TOPK_FEW(E_)                                                              \
-  do {                                                                            \
-    if (pb.k <= 256) k_few_select<E_, 256><<<g, 64, 0, st>>>(pb, ps, b);          \
-    else k_few_select<E_, 512><<<g, 64, 0, st>>>(pb, ps, b);                      \
-  } while (0)
-  if (nb <= 512) TOPK_FEW(8);
-  else if (nb <= 1024) TOPK_FEW(16);
-  else if (nb <= 2048) TOPK_FEW(32);
-  else TOPK_FEW(64);
-#undef TOPK_FEW
-  k_tile_select_redo<<<REDO_BLOCKS, 256, (size_t)pow2_at_least(pb.k) * 8, st>>>(pb, ps, b.scores, few_row_len(pb.Lk), b.sel,
-                                                                              b.redo_list, b.redo_count);
-  return hipGetLastError();
-}
-
 // ------------------------------------------------------------------ fused path: fallback
 // Exact recomputation of the rows on the redo list (candidate buffer overflow, or
 // a threshold that turned out above the row's k-th score). The first REDO_CAP rows
@@ -2040,6 +1504,7 @@ __global__ __launch_bounds__(256) void k_redo_select(Problem pb, Pass ps, PassBu
   __shared__ uint32_t ccount;
   wg_row_select(bufs.scores + r * pb.Lk, nv, k_eff, pb.k, (pb.Lk & 3) == 0, cand, sbuf, hist, misc, &ccount,
                 bufs.sel + p * pb.k, nullptr);
+  if (!bufs.sel_sorted) write_selection(pb, rr.bh * pb.Lq + rr.i, k_eff, threadIdx.x, 256, [&](int64_t t) { return sbuf[t]; });
 }
 
 template <typename T>
@@ -2073,6 +1538,7 @@ __global__ __launch_bounds__(256) void k_redo_rest(Problem pb, Pass ps, PassBufs
     __syncthreads();
     auto getkey = [&](int64_t e) { return make_key(row[e], (uint32_t)e); };
     team_topk<256>(getkey, nv, k_eff, (uint32_t)pb.k, sbuf, pow2_at_least(k_eff), hist, misc, bufs.sel + p * pb.k);
+    if (!bufs.sel_sorted) write_selection(pb, rr.bh * pb.Lq + rr.i, k_eff, threadIdx.x, 256, [&](int64_t t) { return sbuf[t]; });
     __syncthreads();
   }
 }
@@ -2153,7 +1619,7 @@ __device__ unsigned long long g_bad_indices = 0;
 #endif
 
 template <typename T, int NSLICES>
-__device__ __forceinline__ void finalize_row(const Problem& pb, const Pass& ps, const uint64_t* sel, int64_t p,
+__device__ __forceinline__ void finalize_row(const Problem& pb, const Pass& ps, const uint64_t* sel, bool sorted, int64_t p,
                                              float* w, uint32_t* jj, int slice) {
   constexpr int E = Vec16<T>::E;
   const RowRef rr = row_of(pb, ps, p);
@@ -2177,7 +1643,7 @@ __device__ __forceinline__ void finalize_row(const Problem& pb, const Pass& ps, 
       if ((uint32_t)j > jmax) atomicAdd(&g_bad_indices, 1ull);
 #endif
     }
-    if (slice == 0) {
+    if (slice == 0 && sorted) {  // an unsorted selection's outputs were written by its select
       if (pb.idx_out) pb.idx_out[grow * pb.k + t] = j;
       if (pb.score_out) pb.score_out[grow * pb.k + t] = s;
     }
@@ -2185,7 +1651,11 @@ __device__ __forceinline__ void finalize_row(const Problem& pb, const Pass& ps, 
   __syncthreads();
   float inv = 1.f;
   if (pb.act == ACT_SOFTMAX) {
-    const float m = w[0];
+    float m = w[0];
+    if (!sorted) {
+      for (int64_t t = lane; t < k_eff; t += 64) m = __builtin_elementwise_maximum(m, w[t]);
+      m = wave_extreme_f32_full<true>(m);
+    }
     const float c = pb.scale * 1.4426950408889634f;  // exp(x) = exp2(x * log2 e)
     float sum = 0.f;
     for (int64_t t = lane; t < k_eff; t += 64) {
@@ -2266,7 +1736,7 @@ __device__ __forceinline__ void finalize_row(const Problem& pb, const Pass& ps, 
 }
 
 template <typename T, int NSLICES>
-__global__ __launch_bounds__(64) void k_finalize(Problem pb, Pass ps, const uint64_t* sel) {
+__global__ __launch_bounds__(64) void k_finalize(Problem pb, Pass ps, const uint64_t* sel, int sorted) {
   static_assert(8 % NSLICES == 0, "slices are dealt to the 8 XCDs");
   extern __shared__ float fsh[];
   const int64_t G = gridDim.x, bid = blockIdx.x;
@@ -2282,7 +1752,7 @@ __global__ __launch_bounds__(64) void k_finalize(Problem pb, Pass ps, const uint
     // value rows) run on one XCD
     p = (G % 8 == 0) ? (bid % 8) * (G / 8) + bid / 8 : bid;
   }
-  finalize_row<T, NSLICES>(pb, ps, sel, p, fsh, (uint32_t*)(fsh + pb.k), slice);
+  finalize_row<T, NSLICES>(pb, ps, sel, sorted != 0, p, fsh, (uint32_t*)(fsh + pb.k), slice);
 }
 
 // Few rows (at most 128 in the call, 512 with k >= 128): eight waves per row and 128-byte
@@ -2291,7 +1761,7 @@ __global__ __launch_bounds__(64) void k_finalize(Problem pb, Pass ps, const uint
 // slice) leaves 24 rows of 256 survivors, d = 768, to 96 waves: 36 -> 7 us; 128 rows of 512,
 // d = 1024: 46 -> 21 us; 200 rows of 64, d = 256, are better off there: 8 / 10 us.
 template <typename T>
-__global__ __launch_bounds__(512) void k_finalize_few(Problem pb, Pass ps, const uint64_t* sel, int slices) {
+__global__ __launch_bounds__(512) void k_finalize_few(Problem pb, Pass ps, const uint64_t* sel, int sorted, int slices) {
   constexpr int E = Vec16<T>::E, U = 4;
   extern __shared__ float fsh[];
   __shared__ float wsum[8];
@@ -2321,13 +1791,17 @@ __global__ __launch_bounds__(512) void k_finalize_few(Problem pb, Pass ps, const
       if ((uint32_t)j > jmax) atomicAdd(&g_bad_indices, 1ull);
 #endif
     }
-    if (slice == 0) {
+    if (slice == 0 && sorted) {  // an unsorted selection's outputs were written by its select
       if (pb.idx_out) pb.idx_out[grow * pb.k + t] = j;
       if (pb.score_out) pb.score_out[grow * pb.k + t] = s;
     }
   }
   __syncthreads();
-  const float m = w[0];
+  float m = w[0];
+  if (!sorted) {
+    for (int t = lane; t < k_eff; t += 64) m = __builtin_elementwise_maximum(m, w[t]);
+    m = wave_extreme_f32_full<true>(m);
+  }
   __syncthreads();
   const bool softmax = pb.act == ACT_SOFTMAX;
   const float c = pb.scale * 1.4426950408889634f;  // exp(x) = exp2(x * log2 e)
@@ -2483,13 +1957,18 @@ hipError_t launch_tile_scores(const Problem& pb, const Pass& ps, const PassBufs&
   return hipGetLastError();
 }
 
+hipError_t launch_tile_redo(const Problem& pb, const Pass& ps, const PassBufs& b, int64_t row_len, hipStream_t st) {
+  k_tile_select_redo<<<REDO_BLOCKS, 256, (size_t)pow2_at_least(pb.k) * 8, st>>>(pb, ps, b.scores, row_len, b.sel, b.redo_list,
+                                                                              b.redo_count);
+  return hipGetLastError();
+}
+
 hipError_t launch_tile_select(const Problem& pb, const Pass& ps, const PassBufs& b, hipStream_t st) {
   const int P = pow2_at_least(pb.k);
   if (pb.k <= 256 && pb.Lk <= TSW_MAX_N) {
     k_tile_select_wave<<<(unsigned)pass_rows(pb, ps), 64, 0, st>>>(pb, ps, b.scores, b.sel, b.redo_list,
                                                                     b.redo_count);
-    k_tile_select_redo<<<REDO_BLOCKS, 256, (size_t)P * 8, st>>>(pb, ps, b.scores, pb.Lk, b.sel, b.redo_list,
-                                                                  b.redo_count);
+    return launch_tile_redo(pb, ps, b, pb.Lk, st);
   } else {
     k_tile_select<<<(unsigned)pass_rows(pb, ps), 256, (size_t)P * 8, st>>>(pb, ps, b.scores, b.sel, b.redo_count);
   }
@@ -2566,8 +2045,10 @@ hipError_t launch_fused_scan(const Problem& pb, const Pass& ps, const PassBufs& 
 }
 
 hipError_t launch_cand_select(const Problem& pb, const Pass& ps, const PassBufs& b, hipStream_t st) {
-  if (b.caph > 512) k_cand_select<true><<<(unsigned)pass_rows(pb, ps), 64, 0, st>>>(pb, ps, b);
-  else k_cand_select<false><<<(unsigned)pass_rows(pb, ps), 64, 0, st>>>(pb, ps, b);
+  if (!b.sel_sorted) return launch_keep_select(pb, ps, b, st);
+  const unsigned g = (unsigned)pass_rows(pb, ps);
+  if (b.caph > 512) k_cand_select<true><<<g, 64, 0, st>>>(pb, ps, b);
+  else k_cand_select<false><<<g, 64, 0, st>>>(pb, ps, b);
   return hipGetLastError();
 }
 
@@ -2595,8 +2076,8 @@ hipError_t launch_finalize(const Problem& pb, const Pass& ps, const PassBufs& b,
   if (rows <= 128 || (rows <= 512 && pb.k >= 128)) {  // see k_finalize_few
     const int slices = (int)((row + 127) / 128);
     const unsigned gf = (unsigned)(pass_rows(pb, ps) * slices);
-    if (pb.dtype == T_BF16) k_finalize_few<uint16_t><<<gf, 512, sh, st>>>(pb, ps, b.sel, slices);
-    else k_finalize_few<float><<<gf, 512, sh, st>>>(pb, ps, b.sel, slices);
+    if (pb.dtype == T_BF16) k_finalize_few<uint16_t><<<gf, 512, sh, st>>>(pb, ps, b.sel, b.sel_sorted, slices);
+    else k_finalize_few<float><<<gf, 512, sh, st>>>(pb, ps, b.sel, b.sel_sorted, slices);
     return hipGetLastError();
   }
   int S = 1;
@@ -2607,10 +2088,10 @@ hipError_t launch_finalize(const Problem& pb, const Pass& ps, const PassBufs& b,
   if (g > 0x7FFFFFFF) return hipErrorInvalidValue;
 #define TOPK_FINALIZE(T_)                                                                   \
   do {                                                                                      \
-    if (S == 8) k_finalize<T_, 8><<<(unsigned)g, 64, sh, st>>>(pb, ps, b.sel);              \
-    else if (S == 4) k_finalize<T_, 4><<<(unsigned)g, 64, sh, st>>>(pb, ps, b.sel);         \
-    else if (S == 2) k_finalize<T_, 2><<<(unsigned)g, 64, sh, st>>>(pb, ps, b.sel);         \
-    else k_finalize<T_, 1><<<(unsigned)g, 64, sh, st>>>(pb, ps, b.sel);                     \
+    if (S == 8) k_finalize<T_, 8><<<(unsigned)g, 64, sh, st>>>(pb, ps, b.sel, b.sel_sorted);              \
+    else if (S == 4) k_finalize<T_, 4><<<(unsigned)g, 64, sh, st>>>(pb, ps, b.sel, b.sel_sorted);         \
+    else if (S == 2) k_finalize<T_, 2><<<(unsigned)g, 64, sh, st>>>(pb, ps, b.sel, b.sel_sorted);         \
+    else k_finalize<T_, 1><<<(unsigned)g, 64, sh, st>>>(pb, ps, b.sel, b.sel_sorted);                     \
   } while (0)
   if (pb.dtype == T_BF16) TOPK_FINALIZE(uint16_t);
   else TOPK_FINALIZE(float);

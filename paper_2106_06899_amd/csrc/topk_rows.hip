@@ -67,19 +67,7 @@ __device__ __forceinline__ f32x4 mfma_step(uint4 a, uint4 b, f32x4 acc, float) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.w), __uint_as_float(b.w), acc, 0, 0, 0);
 }
 
-// The maximum or minimum of x over a wave whose lanes are all active (NaN if any is), and
-// the sum: every lane holds its row of 16 lanes' after four DPP steps.
-template <bool MAX>
-__device__ __forceinline__ float rows_wave_extreme(float x) {
-  auto op = [](float u, float v) { return MAX ? __builtin_elementwise_maximum(u, v) : __builtin_elementwise_minimum(u, v); };
-  auto dpp = [](float v, auto ctrl) { return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), decltype(ctrl)::value, 0xF, 0xF, false)); };
-  x = op(x, dpp(x, std::integral_constant<int, 0xB1>{}));   // quad [1,0,3,2]
-  x = op(x, dpp(x, std::integral_constant<int, 0x4E>{}));   // quad [2,3,0,1]
-  x = op(x, dpp(x, std::integral_constant<int, 0x141>{}));  // row_half_mirror
-  x = op(x, dpp(x, std::integral_constant<int, 0x140>{}));  // row_mirror
-  auto at = [&](int l) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), l)); };
-  return op(op(at(0), at(16)), op(at(32), at(48)));
-}
+// The sum of x over a wave whose lanes are all active.
 __device__ __forceinline__ float rows_wave_sum(float x) {
   auto dpp = [](float v, auto ctrl) { return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), decltype(ctrl)::value, 0xF, 0xF, false)); };
   x += dpp(x, std::integral_constant<int, 0xB1>{});
@@ -235,8 +223,8 @@ __global__ __launch_bounds__(64 * E, 4) void k_rows(RowsArgs a) {
           mx = __builtin_elementwise_maximum(mx, s[e]);
         }
       }
-      mx = rows_wave_extreme<true>(mx);
-      mn = rows_wave_extreme<false>(mn);
+      mx = wave_extreme_f32_full<true>(mx);
+      mn = wave_extreme_f32_full<false>(mn);
       // bounds of the k-th largest score: at least k are >= lo (clo of them), fewer than k
       // are >= hi (chi of them)
       float lo = mn, hi = ord_to_f32(ord_u32(mx) + 1u);
