@@ -88,6 +88,90 @@ __global__ __launch_bounds__(256) void k_tile_scores(Problem pb, Pass ps, float*
   }
 }
 
+// fp32 inputs with d % 16 == 0: 128 queries x 64 keys per workgroup on the fp32 matrix
+// instruction (32-bit products and sums), 32 x 64 per wave as blocks of 16 x 16 with A = K and
+// B = Q^T. Operands come straight from global memory, 16 bytes per lane (lane group g takes
+// features 4 g .. 4 g + 3 of every 16: the contraction is free to take them in any order); the
+// six parts of the next 16 features are in flight while the 32 instructions of the current
+// ones run. Bound by the latency of those loads at three waves a SIMD (142 VGPRs; at four the
+// kernel spills and takes 65 us). 8 heads of 1511, d = 96, causal, against 64 x 64 tiles of
+// scalar FMAs from LDS: 71 -> 52 us; storing each lane's own four keys instead of whole
+// rows through LDS: 55 us.
+typedef float f32x4 __attribute__((__vector_size__(16)));
+__global__ __launch_bounds__(256, 3) void k_tile_scores_f32(Problem pb, Pass ps, float* S) {
+  constexpr int TQ = 128, TK = 64;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, n = lane & 15,
+            g = lane >> 4;
+  const int64_t NG = gridDim.x, bid = blockIdx.x;
+  const int64_t wg = (NG % 8 == 0) ? (bid % 8) * (NG / 8) + bid / 8 : bid;
+  const int64_t nq = (pb.C + TQ - 1) / TQ, nk = (pb.Lk + TK - 1) / TK;
+  const int64_t qt = wg % nq, kt = (wg / nq) % nk, cl = wg / (nq * nk);
+  const int64_t key0 = kt * TK, r0 = qt * TQ + wave * 32;
+  const int64_t id = ps.c0 + cl, bh = id / ps.nchunk, c = id - bh * ps.nchunk, i0 = pb.q0 + c * pb.C;
+  if (r0 >= pb.C || i0 + r0 >= pb.q1) return;  // whole wave; no barrier follows
+  if (pb.causal) {
+    const int64_t last = r0 + 31 < pb.C ? r0 + 31 : pb.C - 1;
+    if (key0 > i0 + last) return;  // entirely above the diagonal: never read
+  }
+  const int d = (int)pb.d;
+  const float* Kh = (const float*)pb.K + bh * pb.kv_head_stride + key0 * d;
+  const float* Qh = (const float*)pb.Q + (bh * pb.Lq + i0 + r0) * d;
+  const int kl = (int)(pb.Lk - key0 < TK ? pb.Lk - key0 : TK) - 1;
+  const int64_t in_chunk = pb.C - r0, in_rows = pb.q1 - i0 - r0;
+  const int ql = (int)(in_chunk < in_rows ? (in_chunk < 32 ? in_chunk : 32) : (in_rows < 32 ? in_rows : 32)) - 1;
+  uint32_t ko[4], qo[2];  // keys past Lk and rows past the chunk repeat the last
+#pragma unroll
+  for (int t = 0; t < 4; ++t) ko[t] = (uint32_t)(min(16 * t + n, kl) * d + 4 * g);
+#pragma unroll
+  for (int t = 0; t < 2; ++t) qo[t] = (uint32_t)(min(16 * t + n, ql) * d + 4 * g);
+  f32x4 acc[4][2];
+#pragma unroll
+  for (int a = 0; a < 4; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b) acc[a][b] = (f32x4){};
+  f32x4 kf[2][4], qf[2][2];
+  auto load = [&](int f, int buf) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t) kf[buf][t] = *(const f32x4*)(Kh + ko[t] + f);
+#pragma unroll
+    for (int t = 0; t < 2; ++t) qf[buf][t] = *(const f32x4*)(Qh + qo[t] + f);
+  };
+  auto step = [&](int buf) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+          acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[buf][a][e], qf[buf][b][e], acc[a][b], 0, 0, 0);
+  };
+  load(0, 0);
+  for (int f = 0; f < d; f += 32) {
+    if (f + 16 < d) load(f + 16, 1);
+    step(0);
+    if (f + 16 >= d) break;
+    if (f + 32 < d) load(f + 32, 0);
+    step(1);
+  }
+  // Lane: query n of block b, keys 4 g .. 4 g + 3 of block a. Through LDS, so that each store
+  // is one query's 64 keys side by side (a row of the tile need not start at 16 bytes).
+  __shared__ float stash[4][16 * 68];
+  float* sw = stash[wave];
+  const int64_t key = key0 + lane;
+#pragma unroll
+  for (int b = 0; b < 2; ++b) {
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int a = 0; a < 4; ++a) *(f32x4*)(sw + n * 68 + 16 * a + 4 * g) = acc[a][b];
+    __builtin_amdgcn_wave_barrier();
+    for (int r = 0; r < 16; ++r) {
+      const int64_t lr = r0 + 16 * b + r, i = i0 + lr;
+      if (lr >= pb.C || i >= pb.q1) break;
+      if (key < valid_keys(pb, i)) S[(cl * pb.C + lr) * pb.Lk + key] = sw[r * 68 + lane];
+    }
+  }
+}
+
 // ------------------------------------------------------------------ chunk-tile path: MFMA scores
 // bf16 inputs with d % 32 == 0: a 128-query x 256-key tile per workgroup, the
 // feature dimension consumed 32 at a time. Each slice of Q (128 rows x 64 bytes)
@@ -1947,6 +2031,13 @@ hipError_t launch_tile_scores(const Problem& pb, const Pass& ps, const PassBufs&
     const int64_t g = ((pb.Lk + TSM_TK - 1) / TSM_TK) * ((pb.C + TSM_TQ - 1) / TSM_TQ) * ps.nc;
     if (g > 0x7FFFFFFF) return hipErrorInvalidValue;
     k_tile_scores_mfma<0><<<(unsigned)g, 256, 0, st>>>(pb, ps, b);
+    return hipGetLastError();
+  }
+  // 16-byte loads of whole groups of 16 features; a one-dimensional grid (256 threads each, below
+  // 2^32 in all). Other rows and types keep the scalar kernel.
+  const int64_t g = ((pb.Lk + 63) / 64) * ((pb.C + 127) / 128) * ps.nc;
+  if (pb.dtype == T_F32 && pb.d % 16 == 0 && g < (1 << 24)) {
+    k_tile_scores_f32<<<(unsigned)g, 256, 0, st>>>(pb, ps, b.scores);
     return hipGetLastError();
   }
   dim3 grid((unsigned)((pb.Lk + 63) / 64), (unsigned)((pb.C + 63) / 64), (unsigned)ps.nc);

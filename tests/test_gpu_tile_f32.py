@@ -1,0 +1,29 @@
+"""GPU tests of the fp32 score tiles (rows beyond the short-row kernel, d a multiple of 16):
+against the fp64 oracle around the 128-query, 32-query and 64-key tile edges, the 16-feature
+steps and the diagonal, and the same bits whatever the chunk."""
+import pytest
+import torch
+
+from paper_2106_06899_amd import workloads as wl
+from tests import parity
+
+pytestmark = pytest.mark.gpu
+
+# (H, Lq, Lk, d, k, chunk, causal); d = 8 keeps the scalar kernel
+CASES = [
+    (1, 1, 1025, 16, 5, 1, False), (2, 33, 1087, 48, 33, 32, False), (1, 129, 1089, 96, 100, 129, False),
+    (2, 1100, 1100, 64, 40, 127, True), (1, 70, 1028, 272, 12, 64, False), (3, 31, 63, 16, 7, 5, False),
+    (1, 300, 130, 256, 20, 128, True), (1, 40, 1200, 8, 9, 40, False),
+]
+
+
+@pytest.mark.parametrize("case", CASES)
+def test_fp32_score_tiles(case):
+    H, Lq, Lk, d, k, chunk, causal = case
+    w = wl.WORKLOADS["c1"].scaled(H=H, Lq=Lq, Lk=Lk, d=d, k=k, chunk=chunk, causal=causal)
+    print("[case]", w, flush=True)
+    x = wl.make_inputs(w)
+    out, idx, _ = parity.run_attn(w, x)
+    parity.check_attn(w, x, out, idx, rows=parity.sample_attn_rows(w, min(300, H * Lq), seed=6))
+    other = parity.run_attn(w.scaled(chunk=50), x, debug=False)
+    assert torch.equal(other, out)
