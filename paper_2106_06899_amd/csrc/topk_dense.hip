@@ -22,7 +22,7 @@
 // Bound by vector instructions: per tile and wave 32 exponentials (512 cycles) and about
 // 160 others (640) beside 16 MFMAs (512), which this chip overlaps only in part (1670
 // cycles measured). Against V transposed through registers with 2-byte LDS writes, the
-// library exp2f and a rescale in every tile: 12 heads of 8192 tokens, d = 64: 424 -> 305 us.
+// library exp2f and a rescale in every tile: 12 heads of 8192 tokens, d = 64: 424 -> 269 us.
 // (Taking a new maximum over only once it exceeds the old by 2^8 in weight ran 290 us, but
 // the largest weight is then not exactly 1 and its rounding shows: 2.34e-3 against 2.28e-3.)
 #include "topk_internal.h"
