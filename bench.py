@@ -559,7 +559,7 @@ def main():
                     "tflops": flops / ((score_step_ms + sel_ms) / 1e3) / 1e12}
     score_select["frac"] = score_select["tflops"] / PEAK_BF16_TFLOPS
     core = None
-    if path == 1 and w.kind == "attn" and w.d == 64 and 32 < w.k <= 64 and not w.causal:
+    if path == 1 and w.kind == "attn" and w.Lk > 1024 and w.d == 64 and 32 < w.k <= 64 and not w.causal:
         # the scan's score-core ablation at the same launch shape (no filter): its ceiling
         for abl in (False, True):
             tk.scan_ablation(q, k, w.k, w.chunk, score_only=abl)  # warm-up
