@@ -15,14 +15,16 @@
 // stored, and every sum runs in a fixed order (the order of a cell's list, which is not
 // fixed, only says where its values go).
 //
-// The sparse operand keeps its 32 bits: every value is split into the sum of two bf16
-// numbers (16 significant bits or more against the 8 of the operand it meets and of the
-// result; errors against 64 bits are those of the gathers, 1.7e-3, to all digits
-// measured). A result that is not finite (an infinite or NaN row that a zero met) is
-// computed again for its row alone, from its own pairs.
+// The sparse operand keeps its 32 bits: it lies in LDS as floats, and each wave takes the
+// values apart into three bf16 numbers that add up to them exactly, so that a product differs
+// from a gather's only by the order of its 32-bit sums: 48 heads of 1024, d = 64, 2.0e-4 of
+// d_K's stored values are not the 64-bit result rounded, by the gathers 1.7e-4 (by two bf16
+// numbers, 16 or 17 bits: 2.4e-3, and the step of 16384 tokens below takes 2040 us for 2425).
+// A result that is not finite (an infinite or NaN row that a zero met) is computed again for
+// its row alone, from its own pairs.
 //
-// Bound by latency (two waves a SIMD: 74 KB of LDS a workgroup) and, for wide rows, by the
-// matrix instructions. Whole backward pass, lists -> cells: 16384 tokens, d_model 768, 512
+// Bound by latency (two waves a SIMD: 70 KB of LDS a workgroup) and, for wide rows, by the
+// matrix instructions and the taking apart, about 45 vector instructions per 12 of them. Whole backward pass, lists -> cells: 16384 tokens, d_model 768, 512
 // of 4096 units: 5290 -> 1040 us; of 16384: 6230 -> 2760; 48 heads of 1024 tokens, d = 64,
 // k = 64: 264 -> 195; 16 heads of 2048, d = 128, k = 128: 390 -> 256.
 #include "topk_device.h"
@@ -40,10 +42,24 @@ __device__ __forceinline__ uint32_t pack2_bf16(float x, float y) {  // nearest-e
   return __builtin_bit_cast(uint32_t, v);
 }
 
-// x as the sum of two bf16 numbers, the first in the low half of the word
-__device__ __forceinline__ uint32_t split2_bf16(float x) {
-  const uint32_t h = pack2_bf16(x, 0.f);
-  return pack2_bf16(0.f, x - __uint_as_float(h << 16)) | h;
+// Eight floats as the exact sums of three bf16 numbers each: the leading 8 significant bits,
+// the next 8 and the last 8 (cut off, not rounded, so that nothing is left over). Two values'
+// halves are paired up by one byte permute.
+__device__ __forceinline__ void split3_bf16(const f32x4& x0, const f32x4& x1, bf16x8 (&part)[3]) {
+  float r[8];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) r[e] = x0[e], r[4 + e] = x1[e];
+#pragma unroll
+  for (int p = 0; p < 3; ++p) {
+    uint32_t w[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      w[e] = __builtin_amdgcn_perm(__float_as_uint(r[2 * e + 1]), __float_as_uint(r[2 * e]), 0x07060302u);
+    part[p] = __builtin_bit_cast(bf16x8, make_uint4(w[0], w[1], w[2], w[3]));
+    if (p < 2)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) r[e] -= __uint_as_float(__float_as_uint(r[e]) & 0xFFFF0000u);
+  }
 }
 // A workgroup barrier for LDS alone: global loads stay in flight across it.
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
@@ -228,10 +244,9 @@ template <int WC, bool TRANS>
 __global__ __launch_bounds__(256, 2) void k_cells_mm(MmArgs a) {
   constexpr int WR = 4 / WC;       // waves along the rows of the tile
   constexpr int RT = 8 / WR;       // 16-row tiles per wave
-  // the sparse operand of two cells in turn: a bf16 tile of the values' first parts and one
-  // of their second parts
-  constexpr int TS = 72, PART = 128 * TS;  // row stride, elements per tile
-  __shared__ __attribute__((aligned(16))) uint16_t tiles[2][2 * PART];
+  // the sparse operand of two cells in turn, in 32 bits
+  constexpr int TS = 68, TILE = 128 * TS;  // row stride, elements per tile
+  __shared__ __attribute__((aligned(16))) float tiles[2][TILE];
   __shared__ int bad_lds[128];
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, n = lane & 15,
             g = lane >> 4;
@@ -262,11 +277,8 @@ __global__ __launch_bounds__(256, 2) void k_cells_mm(MmArgs a) {
   for (int r = 0; r < RT; ++r)
 #pragma unroll
     for (int c = 0; c < 4; ++c) acc[r][c] = (f32x4){};
-  for (int i = tid; i < 4 * PART / 8; i += 256) ((f32x4*)&tiles[0][0])[i] = (f32x4){};
-  // this lane's operand rows within a whole cell: 8 g + e of each 32
-  uint32_t boff[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) boff[e] = (uint32_t)((8 * g + e) * a.d + colr);
+  for (int i = tid; i < 2 * TILE / 4; i += 256) ((f32x4*)&tiles[0][0])[i] = (f32x4){};
+  const uint32_t boff = (uint32_t)(8 * g * a.d + colr);  // this lane's operand rows of a whole cell: 8 g + e of each 32
   // entries of a cell held per thread, read while the cell before is multiplied; the
   // previous cell's, to clear its tile
   constexpr int U = 4;
@@ -325,23 +337,15 @@ __global__ __launch_bounds__(256, 2) void k_cells_mm(MmArgs a) {
       const uint32_t r = e >> 6 & 63u, k = e & 63u, h = e >> 12 << 6;
       return TRANS ? (k + h) * TS + r : (r + h) * TS + k;
     };
-    auto put = [&](uint16_t* t, uint32_t e, float v) {
-      const uint32_t p = place(e), x = split2_bf16(v);
-      t[p] = (uint16_t)x;
-      t[PART + p] = (uint16_t)(x >> 16);
-    };
-    auto clear = [&](uint16_t* t, uint32_t e) {
-      const uint32_t p = place(e);
-      t[p] = 0;
-      t[PART + p] = 0;
-    };
+    auto put = [&](float* t, uint32_t e, float v) { t[place(e)] = v; };
+    auto clear = [&](float* t, uint32_t e) { t[place(e)] = 0.f; };
     uint64_t todo = __ballot(ln0 + ln1 > 0);
     const uint64_t rep = __ballot(lrep != 0);  // cells with keys listed twice in a row
     // operand rows of cell c (rows past N repeat the last: their tile columns are 0)
     auto brow = [&](int c, int o, int e) {  // this lane's e-th row from row o on
       const uint16_t* Bc = B + (int64_t)c * 64 * a.d;
       const int jmax = (int)(a.N - 1 - (int64_t)c * 64);
-      return Bc + (jmax >= 63 ? (uint32_t)(o * a.d) + boff[e] : (uint32_t)(min(o + 8 * g + e, jmax) * a.d + colr));
+      return jmax >= 63 ? Bc + (o + e) * a.d + boff : Bc + (uint32_t)(min(o + 8 * g + e, jmax) * a.d + colr);
     };
     uint32_t bq[2][8][2];
     auto load_b = [&](int c) {
@@ -358,7 +362,7 @@ __global__ __launch_bounds__(256, 2) void k_cells_mm(MmArgs a) {
     while (todo) {
       const int c = cb0 + __builtin_ctzll(todo);
       todo &= todo - 1;
-      uint16_t* cur = tiles[buf];
+      float* cur = tiles[buf];
       buf ^= 1;
       // with registers to spare the next cell's entries are asked for before this cell's
       // are put in place, otherwise after
@@ -393,13 +397,12 @@ __global__ __launch_bounds__(256, 2) void k_cells_mm(MmArgs a) {
           uint32_t e;
           float v;
           fetch(i, e, v);
-          const uint16_t* th = cur + place(e);
-          put(cur, e, v + bf16_to_f32(th[0]) + bf16_to_f32(th[PART]));
+          cur[place(e)] += v;
         }
       }
       lds_barrier();  // the tile is complete; every wave is done with the other one
       // clear the other tile's entries, then keep this cell's for the next turn
-      uint16_t* oth = tiles[buf];
+      float* oth = tiles[buf];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         if (eo[u] != 0xFFFFFFFFu) clear(oth, eo[u]);
@@ -444,12 +447,13 @@ __global__ __launch_bounds__(256, 2) void k_cells_mm(MmArgs a) {
           }
 #pragma unroll
           for (int r = 0; r < RT; ++r) {
-            const uint16_t* o = cur + ((wr * RT + r) * 16 + n) * TS + 32 * kb + 8 * g;
-            const bf16x8 ph = *(const bf16x8*)o, pl = *(const bf16x8*)(o + PART);
+            const float* o = cur + ((wr * RT + r) * 16 + n) * TS + 32 * kb + 8 * g;
+            bf16x8 part[3];
+            split3_bf16(*(const f32x4*)o, *(const f32x4*)(o + 4), part);
 #pragma unroll
-            for (int q = 0; q < 4; ++q) acc[r][q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ph, bv[q], acc[r][q], 0, 0, 0);
+            for (int p = 0; p < 3; ++p)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) acc[r][q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pl, bv[q], acc[r][q], 0, 0, 0);
+              for (int q = 0; q < 4; ++q) acc[r][q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(part[p], bv[q], acc[r][q], 0, 0, 0);
           }
         }
       if (todo) load_b(cb0 + __builtin_ctzll(todo));  // the next cell's, while its entries are put in place

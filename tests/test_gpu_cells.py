@@ -139,3 +139,33 @@ def test_cells_need_more_workspace_than_lists():
     torch.cuda.synchronize()
     for p, r in zip(out, want):
         assert torch.equal(p, r)
+
+
+@pytest.mark.parametrize("dm", [256, 288, 1024])
+def test_cells_keep_32_bits(dm):
+    """Weights and score gradients of 18 significant bits that cancel to their last bits: exact in 32
+    bits (products of 18-bit integers and powers of two, sums that stay below 2^24), lost in 16."""
+    N, dff, k = 300, 700, 30
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    pow2 = lambda *s: (torch.randint(0, 2, s, generator=gen, device="cuda") * 2 - 1) * 2.0 ** torch.randint(-1, 2, s, generator=gen, device="cuda")
+    big, near = 2.0 ** 17 + 257, 2.0 ** 17 + 255
+    row = lambda *v: torch.cat([torch.tensor(v, device="cuda"), torch.zeros(dm - len(v), device="cuda")])
+    x, w1, w2, g = pow2(N, dm), pow2(dff, dm), pow2(dff, dm), pow2(N, dm)
+    idx = torch.full((N, k), -1, dtype=torch.int32, device="cuda")
+    dots = torch.ones(N, k, device="cuda")
+    # units 0 .. 29, kept by tokens 0 and 100: their score gradients are `big` and `-near`
+    x[100] = x[0]
+    w2[:30], g[0], g[100] = row(512, 256, 1), row(256, 1, 1), row(-256, 0, -255)
+    idx[[0, 100]] = torch.arange(30, dtype=torch.int32, device="cuda")
+    # units 600 .. 629, kept by tokens 5 and 290 with weights `big` and `near`
+    g[290] = -g[5]
+    idx[[5, 290]] = torch.arange(600, 630, dtype=torch.int32, device="cuda")
+    dots[5], dots[290] = big, near
+    # token 70 keeps units 300 and 500: score gradients `big` and `-near`
+    w1[500] = w1[300]
+    w2[300], w2[500], g[70] = row(512, 256, 1), row(-512, 0, -255), row(256, 1, 1)
+    idx[70, 3], idx[70, 9] = 300, 500
+    dx, dw1, dw2 = tk.ffn_backward(*(t.bfloat16() for t in (x, w1, w2)), idx, dots, g.bfloat16())
+    assert torch.equal(dw1[:30].float(), (2 * x[0]).expand(30, -1))
+    assert torch.equal(dw2[600:630].float(), (2 * g[5]).expand(30, -1))
+    assert torch.equal(dx[70].float(), 2 * w1[300])
