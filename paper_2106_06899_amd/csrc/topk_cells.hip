@@ -34,33 +34,6 @@
 
 namespace topk {
 
-typedef float f32x4 __attribute__((__vector_size__(16)));
-
-__device__ __forceinline__ uint32_t pack2_bf16(float x, float y) {  // nearest-even, x in the low half
-  typedef __bf16 bf16x2 __attribute__((__vector_size__(4)));
-  const bf16x2 v = {(__bf16)x, (__bf16)y};
-  return __builtin_bit_cast(uint32_t, v);
-}
-
-// Eight floats as the exact sums of three bf16 numbers each: the leading 8 significant bits,
-// the next 8 and the last 8 (cut off, not rounded, so that nothing is left over). Two values'
-// halves are paired up by one byte permute.
-__device__ __forceinline__ void split3_bf16(const f32x4& x0, const f32x4& x1, bf16x8 (&part)[3]) {
-  float r[8];
-#pragma unroll
-  for (int e = 0; e < 4; ++e) r[e] = x0[e], r[4 + e] = x1[e];
-#pragma unroll
-  for (int p = 0; p < 3; ++p) {
-    uint32_t w[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-      w[e] = __builtin_amdgcn_perm(__float_as_uint(r[2 * e + 1]), __float_as_uint(r[2 * e]), 0x07060302u);
-    part[p] = __builtin_bit_cast(bf16x8, make_uint4(w[0], w[1], w[2], w[3]));
-    if (p < 2)
-#pragma unroll
-      for (int e = 0; e < 8; ++e) r[e] -= __uint_as_float(__float_as_uint(r[e]) & 0xFFFF0000u);
-  }
-}
 // A workgroup barrier for LDS alone: global loads stay in flight across it.
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
@@ -489,7 +462,7 @@ __global__ __launch_bounds__(256, 2) void k_cells_mm(MmArgs a) {
           bad_lds[lm] = 1;
           bad = true;
         }
-        *(uint2*)(out + m * a.d + col0) = make_uint2(pack2_bf16(x0, x1), pack2_bf16(x2, x3));
+        *(uint2*)(out + m * a.d + col0) = make_uint2(pack_bf16(x0, x1), pack_bf16(x2, x3));
       }
     }
   if (!__syncthreads_or(bad)) return;
@@ -512,7 +485,7 @@ __global__ __launch_bounds__(256) void k_cells_reduce(MmArgs a) {
     for (int p = 0; p < a.nsplit; ++p) s += *(const f32x4*)(a.part + (((int64_t)p * a.which + y) * rows + row) * a.d + c);
 #pragma unroll
     for (int q = 0; q < 4; ++q) bad = bad || !(fabsf(s[q]) < INFINITY);
-    *(uint2*)(out + c) = make_uint2(pack2_bf16(s[0], s[1]), pack2_bf16(s[2], s[3]));
+    *(uint2*)(out + c) = make_uint2(pack_bf16(s[0], s[1]), pack_bf16(s[2], s[3]));
   }
   if (__ballot(bad)) cells_fix_row<TRANS>(a, y, bh, m);
 }

@@ -10,6 +10,7 @@
 namespace topk {
 
 typedef __bf16 bf16x8 __attribute__((__vector_size__(16)));
+typedef float f32x4 __attribute__((__vector_size__(16)));
 
 // ------------------------------------------------------------------ scalar helpers
 __device__ __forceinline__ uint32_t ord_u32(float s) {
@@ -44,6 +45,32 @@ template <typename T> __device__ __forceinline__ void store_elem(void* p, int64_
 template <> __device__ __forceinline__ void store_elem<float>(void* p, int64_t e, float v) { ((float*)p)[e] = v; }
 template <> __device__ __forceinline__ void store_elem<uint16_t>(void* p, int64_t e, float v) {
   ((uint16_t*)p)[e] = f32_to_bf16(v);
+}
+
+__device__ __forceinline__ uint32_t pack_bf16(float x, float y) {  // nearest-even, x in the low half
+  typedef __bf16 bf16x2 __attribute__((__vector_size__(4)));
+  const bf16x2 v = {(__bf16)x, (__bf16)y};
+  return __builtin_bit_cast(uint32_t, v);
+}
+
+// Eight floats as the exact sums of three bf16 numbers each: the leading 8 significant bits,
+// the next 8 and the last 8 (cut off, not rounded, so that nothing is left over). Two values'
+// halves are paired up by one byte permute.
+__device__ __forceinline__ void split3_bf16(const f32x4& x0, const f32x4& x1, bf16x8 (&part)[3]) {
+  float r[8];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) r[e] = x0[e], r[4 + e] = x1[e];
+#pragma unroll
+  for (int p = 0; p < 3; ++p) {
+    uint32_t w[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      w[e] = __builtin_amdgcn_perm(__float_as_uint(r[2 * e + 1]), __float_as_uint(r[2 * e]), 0x07060302u);
+    part[p] = __builtin_bit_cast(bf16x8, make_uint4(w[0], w[1], w[2], w[3]));
+    if (p < 2)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) r[e] -= __uint_as_float(__float_as_uint(r[e]) & 0xFFFF0000u);
+  }
 }
 
 // ------------------------------------------------------------------ wave primitives

@@ -19,8 +19,6 @@
 
 namespace topk {
 
-typedef float f32x4 __attribute__((__vector_size__(16)));
-
 template <int RT, int KT>
 __global__ __launch_bounds__(256, RT <= 2 ? 4 : 2) void k_few_scores(Problem pb, Pass ps, PassBufs bufs) {
   constexpr int NS = 16 / KT;  // 32-feature steps whose keys are in flight together

@@ -97,7 +97,6 @@ __global__ __launch_bounds__(256) void k_tile_scores(Problem pb, Pass ps, float*
 // kernel spills and takes 65 us). 8 heads of 1511, d = 96, causal, against 64 x 64 tiles of
 // scalar FMAs from LDS: 71 -> 52 us; storing each lane's own four keys instead of whole
 // rows through LDS: 55 us.
-typedef float f32x4 __attribute__((__vector_size__(16)));
 __global__ __launch_bounds__(256, 3) void k_tile_scores_f32(Problem pb, Pass ps, float* S) {
   constexpr int TQ = 128, TK = 64;
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, n = lane & 15,

@@ -17,8 +17,10 @@
 //     (about 7 steps on Gaussian scores), ties at the k-th score are broken by index. The
 //     row's weights (0 where not selected) replace its scores in LDS;
 //  3. values: out = P V by the matrix instructions, P in full 32 bits: fp32 values by the
-//     fp32 instruction, bf16 values with every weight as the sum of two bf16 numbers
-//     (16 significant bits or more; the products and sums are 32-bit). Each wave takes
+//     fp32 instruction, bf16 values with every weight taken apart into three bf16 numbers
+//     that add up to it exactly (the products and sums are 32-bit; with two numbers, 16 or
+//     17 bits, 96 heads of 512 took 67 us for 69, but 2.2e-3 of the stored values were not
+//     the 64-bit result rounded, against 1.7e-4). Each wave takes
 //     its 64 keys, a value row is read as one contiguous part per lane (column n * CPL + c
 //     is column n of tile c), and the waves' partial sums are added in a fixed order.
 // A dense P V reads each value row once per TR query rows: at 512 keys and k = 64 that is
@@ -27,7 +29,7 @@
 // Bound by the select's vector instructions (about 350 per row at 512 keys, half of the
 // kernel's time) and by latency. Against the launches it replaced (every score written as
 // an 8-byte candidate, selected from global memory, value rows gathered): 96 heads of 512
-// tokens, d = 64, bf16, k = 64: 240 -> 67 us; 48 heads of 1024: 580 -> 184 us with the
+// tokens, d = 64, bf16, k = 64: 240 -> 69 us; 48 heads of 1024: 580 -> 184 us with the
 // cache outputs; one fp32 head of 1024, k = 32 (64 workgroups, latency): 31 -> 25 us of
 // kernel time in one launch instead of five.
 //
@@ -41,8 +43,6 @@
 #include <type_traits>
 
 namespace topk {
-
-typedef float f32x4 __attribute__((__vector_size__(16)));
 
 struct RowsArgs {
   const void* Q;
@@ -78,11 +78,6 @@ __device__ __forceinline__ float rows_wave_sum(float x) {
   return (at(0) + at(16)) + (at(32) + at(48));
 }
 __device__ __forceinline__ float uniform(float x) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x))); }
-__device__ __forceinline__ uint32_t pack_bf16(float x, float y) {  // nearest-even, x in the low half
-  typedef __bf16 bf16x2 __attribute__((__vector_size__(4)));
-  const bf16x2 v = {(__bf16)x, (__bf16)y};
-  return __builtin_bit_cast(uint32_t, v);
-}
 
 // Writes a row's n <= 64 * E distinct selected keys (in scratch, a wave's own LDS) in
 // descending order as indices and raw scores, padded to k with -1 and -inf.
@@ -345,23 +340,8 @@ __global__ __launch_bounds__(64 * E, 4) void k_rows(RowsArgs a) {
         if (mode == 0) bad_lds[r] = 0;
       }
 #pragma unroll
-      for (int c = 0; c < E / 4; ++c) {
-        if (F32 || mode) {
-          *(f32x4*)&row[256 * c + 4 * lane] = (f32x4){s[4 * c], s[4 * c + 1], s[4 * c + 2], s[4 * c + 3]};
-        } else {
-          // a weight as the sum of two bf16 numbers, the first ones in the row's first
-          // half, the second ones in its second half
-          uint32_t h[2], l[2];
-#pragma unroll
-          for (int q = 0; q < 2; ++q) {
-            const float x = s[4 * c + 2 * q], y = s[4 * c + 2 * q + 1];
-            h[q] = pack_bf16(x, y);
-            l[q] = pack_bf16(x - __uint_as_float(h[q] << 16), y - __uint_as_float(h[q] & 0xFFFF0000u));
-          }
-          *(uint2*)&((uint16_t*)row)[256 * c + 4 * lane] = make_uint2(h[0], h[1]);
-          *(uint2*)&((uint16_t*)row)[LKP + 256 * c + 4 * lane] = make_uint2(l[0], l[1]);
-        }
-      }
+      for (int c = 0; c < E / 4; ++c)
+        *(f32x4*)&row[256 * c + 4 * lane] = (f32x4){s[4 * c], s[4 * c + 1], s[4 * c + 2], s[4 * c + 3]};
     }
     __syncthreads();
 
@@ -418,16 +398,15 @@ __global__ __launch_bounds__(64 * E, 4) void k_rows(RowsArgs a) {
         // by byte permutes into the operand's order
 #pragma unroll
         for (int kb = 0; kb < 64; kb += 32) {
-          uint4 ph[RT], pl[RT];
+          bf16x8 p[RT][3];
 #pragma unroll
           for (int r = 0; r < RT; ++r) {
-            const uint16_t* pr = (const uint16_t*)&S[(16 * r + n) * LDS_ROW] + key0 + kb + 8 * g;
-            ph[r] = *(const uint4*)pr;
-            pl[r] = *(const uint4*)(pr + LKP);
+            const float* pr = &S[(16 * r + n) * LDS_ROW + key0 + kb + 8 * g];
+            split3_bf16(*(const f32x4*)pr, *(const f32x4*)(pr + 4), p[r]);
           }
 #pragma unroll
           for (int cp = 0; cp < CPL; cp += CPP) {
-            if (D > 64) __builtin_amdgcn_sched_barrier(0);  // one part's loads at a time: more would spill
+            if (D > 64) __builtin_amdgcn_sched_barrier(0);  // one part's loads at a time: more would spill more
             uint32_t v[8][CPP / 2];
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
@@ -442,10 +421,10 @@ __global__ __launch_bounds__(64 * E, 4) void k_rows(RowsArgs a) {
               const uint4 vf = make_uint4(__builtin_amdgcn_perm(v[1][w], v[0][w], sel), __builtin_amdgcn_perm(v[3][w], v[2][w], sel),
                                           __builtin_amdgcn_perm(v[5][w], v[4][w], sel), __builtin_amdgcn_perm(v[7][w], v[6][w], sel));
 #pragma unroll
-              for (int r = 0; r < RT; ++r) {
-                o[r][cp + c] = mfma_step(ph[r], vf, o[r][cp + c], T());
-                o[r][cp + c] = mfma_step(pl[r], vf, o[r][cp + c], T());
-              }
+              for (int r = 0; r < RT; ++r)
+#pragma unroll
+                for (int t = 0; t < 3; ++t)
+                  o[r][cp + c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(p[r][t], __builtin_bit_cast(bf16x8, vf), o[r][cp + c], 0, 0, 0);
             }
           }
         }
@@ -518,7 +497,9 @@ hipError_t launch_rows_inst(const RowsArgs& a, int64_t BH, hipStream_t st) {
 
 template <typename T, int D>
 hipError_t launch_rows_d(RowsArgs a, int64_t BH, hipStream_t st) {
-  // 32 rows per workgroup halve the reads of keys and values; 16 give twice the
+  // 32 rows per workgroup halve the reads of keys and values (also where their 128
+  // registers spill, bf16 values at d = 96 and 128: 96 heads of 512, d = 128, 104 us against
+  // 117 with 16 rows and no spill; of 1024, d = 96, 279 against 348); 16 give twice the
   // workgroups where 32 would leave CUs idle (fewer than two workgroups for each of the
   // 256), and where 32 rows and the sort scratch would not fit the 160 KB of LDS
   bool tr16 = BH * ((a.Lq + 31) / 32) < 512;

@@ -89,3 +89,19 @@ def test_short_rows_value_rows_not_finite(dtype):
     want = torch.zeros_like(bad)
     want[0, 1, :, 5] = rows
     assert torch.equal(bad, want)
+
+
+@pytest.mark.parametrize("d", [32, 64, 96, 128])
+@pytest.mark.parametrize("dff,N", [(200, 40), (400, 40), (1000, 40), (130, 17000)])
+def test_short_rows_keep_32_bits(dff, N, d):
+    """Weights (ReLU scores) of 18 significant bits that cancel to their last bits: exact in 32 bits,
+    lost in 16."""
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    row = lambda *v: torch.cat([torch.tensor(v, device="cuda"), torch.zeros(d - len(v), device="cuda")])
+    x, w1, w2 = torch.zeros(N, d, device="cuda"), torch.zeros(dff, d, device="cuda"), torch.zeros(dff, d, device="cuda")
+    x[:] = row(256.0, 1, 1)
+    w1[3], w1[dff - 2] = row(512.0, 256, 1), row(512.0, 0, 255)  # scores 2^17 + 257 and 2^17 + 255
+    w2[3] = torch.randint(-100, 100, (d,), generator=gen, device="cuda")
+    w2[dff - 2] = -w2[3]
+    out = tk.ffn(*(t.bfloat16() for t in (x, w1, w2)), 2)
+    assert torch.equal(out.float(), (2 * w2[3]).expand(N, -1))
