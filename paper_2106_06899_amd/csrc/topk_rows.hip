@@ -250,7 +250,7 @@ __global__ __launch_bounds__(64 * E, 4) void k_rows(RowsArgs a) {
         }
       }
       uint64_t take[E];  // lanes whose element e is selected
-      float m = mx;
+      float m = mx, low = lo;  // the row's largest score, a lower bound of the selected ones
       if (finite && clo == k_eff) {
 #pragma unroll
         for (int e = 0; e < E; ++e) take[e] = __builtin_amdgcn_ballot_w64(s[e] >= lo);
@@ -278,6 +278,7 @@ __global__ __launch_bounds__(64 * E, 4) void k_rows(RowsArgs a) {
             chi = c;
           }
         }
+        low = ord_to_f32(ulo);
         // every key above ulo, and of those equal to it the first by index (all of them
         // where exactly k are left)
         int ties = clo == k_eff ? nv : k_eff - chi;
@@ -321,19 +322,28 @@ __global__ __launch_bounds__(64 * E, 4) void k_rows(RowsArgs a) {
       }
       // the weights, 0 where not selected; mode 1 tells unselected keys (-1) from weights of 0
       const float none = mode ? -1.f : 0.f;
+      // bf16 values: weights 2^16 times as large (exactly; undone by inv_lds), so that the last
+      // bit of any float, 2^-149, is one that the last of its three bf16 numbers can hold
+      const float up = F32 || mode ? 1.f : 65536.f;
       float sum = 0.f;
       if (a.act == ACT_SOFTMAX) {
+        if ((low - m) * a.c > -126.f) {
+#pragma unroll
+          for (int e = 0; e < E; ++e) s[e] = __builtin_amdgcn_exp2f((s[e] - m) * a.c);
+        } else {  // weights below the smallest normal number, which the instruction alone makes 0
+#pragma unroll
+          for (int e = 0; e < E; ++e) s[e] = exp2f((s[e] - m) * a.c);
+        }
 #pragma unroll
         for (int e = 0; e < E; ++e) {
-          const float w = __builtin_amdgcn_exp2f((s[e] - m) * a.c);  // at most 2^0; below 2^-126 it is 0
-          s[e] = __builtin_amdgcn_inverse_ballot_w64(take[e]) ? w : none;
+          s[e] = __builtin_amdgcn_inverse_ballot_w64(take[e]) ? s[e] * up : none;
           sum += fmaxf(s[e], 0.f);
         }
         sum = rows_wave_sum(sum);
       } else {
 #pragma unroll
-        for (int e = 0; e < E; ++e) s[e] = __builtin_amdgcn_inverse_ballot_w64(take[e]) ? fmaxf(s[e], 0.f) : none;
-        sum = 1.f;
+        for (int e = 0; e < E; ++e) s[e] = __builtin_amdgcn_inverse_ballot_w64(take[e]) ? fmaxf(s[e], 0.f) * up : none;
+        sum = up;
       }
       if (lane == 0) {
         inv_lds[r] = 1.f / sum;

@@ -105,3 +105,19 @@ def test_short_rows_keep_32_bits(dff, N, d):
     w2[dff - 2] = -w2[3]
     out = tk.ffn(*(t.bfloat16() for t in (x, w1, w2)), 2)
     assert torch.equal(out.float(), (2 * w2[3]).expand(N, -1))
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("Lk,k", [(100, 8), (300, 8), (1000, 8), (200, 200)])
+def test_short_rows_tiny_weights(Lk, k, dtype):
+    """A weight below the smallest normal number (2^-130) against a value of 2^120."""
+    q, kk, v = (torch.zeros(1, 1, n, 64, device="cuda") for n in (40, Lk, Lk))
+    q[..., 0] = 1
+    kk[0, 0, :, 0] = -1e4
+    kk[0, 0, 0, 0], kk[0, 0, 1, 0] = 0, -90.0 * 8
+    v[0, 0, 1] = 2.0 ** 120
+    out = tk.attn(q.to(dtype), kk.to(dtype), v.to(dtype), k, 0, False, 0.125).double()
+    want = np.exp(-90.0) * 2.0 ** 120
+    # the weight has 19 bits; its exponent, 130, an error of 2^-17 at most
+    tol = 2.0 ** -16 + (2.0 ** -8 if dtype == torch.bfloat16 else 0)
+    assert bool(((out - want).abs() <= tol * want).all()), out.flatten()[0]
