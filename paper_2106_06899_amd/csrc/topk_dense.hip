@@ -22,12 +22,16 @@
 // Bound by vector instructions: per tile and wave 32 exponentials (512 cycles) and about
 // 160 others (640) beside 16 MFMAs (512), which this chip overlaps only in part (1670
 // cycles measured). Against V transposed through registers with 2-byte LDS writes, the
-// library exp2f and a rescale in every tile: 12 heads of 8192 tokens, d = 64: 424 -> 269 us.
+// library exp2f and a rescale in every tile: 12 heads of 8192 tokens, d = 64: 424 -> 284 us.
+// The exponential instruction alone makes a weight below 2^-126 zero; a tile whose lowest
+// score leads there adds those weights by themselves (the test for it takes 14 of 284 us).
 // (Taking a new maximum over only once it exceeds the old by 2^8 in weight ran 290 us, but
 // the largest weight is then not exactly 1 and its rounding shows: 2.34e-3 against 2.28e-3.)
 #include "topk_internal.h"
 
 #include <math.h>
+
+#include <type_traits>
 
 namespace topk {
 
@@ -134,14 +138,20 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void k_dense_attn(DenseArgs a
     df32x16 s[2];
 #pragma unroll
     for (int rb = 0; rb < 2; ++rb) s[rb] = block_scores(kb, rb);
+    // the tile's lowest score (masked keys' included: they only choose the exponential below)
+    float low = INFINITY;
+#pragma unroll
+    for (int v = 0; v < 32; v += 2)
+      low = __builtin_elementwise_minimum(__builtin_elementwise_minimum(low, s[v >> 4][v & 15]), s[v >> 4][(v & 15) + 1]);
     if (t * DN_KT + DN_KT > a.Lk || (CAUSAL && t * DN_KT + DN_KT - 1 > q_first + wave * DN_QW)) {
       mask(s[0], t * DN_KT + 4 * half);
       mask(s[1], t * DN_KT + 32 + 4 * half);
     }
     // the tile's maximum of the query (both of its lanes)
-    float mt = __builtin_elementwise_maximum(s[0][0], s[1][0]);
+    float mt = -INFINITY;
 #pragma unroll
-    for (int v = 1; v < 16; ++v) mt = __builtin_elementwise_maximum(mt, __builtin_elementwise_maximum(s[0][v], s[1][v]));
+    for (int v = 0; v < 32; v += 2)
+      mt = __builtin_elementwise_maximum(__builtin_elementwise_maximum(mt, s[v >> 4][v & 15]), s[v >> 4][(v & 15) + 1]);
     mt = __builtin_elementwise_maximum(mt, __shfl_xor(mt, 32, 64));
     // (not <=: for NaN too; queries whose maximum stays multiply by 1)
     if (__builtin_amdgcn_ballot_w64(!(mt <= m_run))) {
@@ -155,35 +165,48 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void k_dense_attn(DenseArgs a
         for (int v = 0; v < 16; ++v) o[db][v] *= alpha;
     }
     const float off = m_run == -INFINITY ? 0.f : m_run * cexp;  // all keys masked so far: weights stay 0
+    auto values = [&](auto tiny) {
+      int at = 4 * half * 2 * D + n * NDB * 2;  // the lane's place in V's tile
+      float bias = -off;
+      if (decltype(tiny)::value) asm volatile("" : "+v"(at), "+v"(bias));  // (nothing of one pass is held for the other)
 #pragma unroll
-    for (int rb = 0; rb < 2; ++rb) {
+      for (int rb = 0; rb < 2; ++rb) {
 #pragma unroll
-      for (int st = 0; st < 2; ++st) {
-        // B: the lane's 8 weights of keys 16 st + {4h..4h+3, 8+4h..8+4h+3} of the block
-        dbf16x8 pb;
+        for (int st = 0; st < 2; ++st) {
+          if (decltype(tiny)::value) __builtin_amdgcn_sched_barrier(0);  // one step's registers at a time
+          // B: the lane's 8 weights of keys 16 st + {4h..4h+3, 8+4h..8+4h+3} of the block
+          dbf16x8 pb;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const float w = __builtin_amdgcn_exp2f(fmaf(s[rb][8 * st + e], cexp, -off));  // below 2^-126 it is 0
-          l_run += w;
-          pb[e] = (__bf16)w;
-        }
-        // A: rows 32 rb + 16 st + the same keys of V, columns n * NDB ..
-        uint32_t vr[8][VW];
+          for (int e = 0; e < 8; ++e) {
+            const float x = fmaf(s[rb][8 * st + e], cexp, bias);
+            const float w = !decltype(tiny)::value ? __builtin_amdgcn_exp2f(x) : x < -126.f ? exp2f(x) : 0.f;
+            l_run += w;
+            pb[e] = (__bf16)w;
+          }
+          // A: rows 32 rb + 16 st + the same keys of V, columns n * NDB ..
+          uint32_t vr[8][VW];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const int key = rb * 32 + 16 * st + (e & 4) * 2 + 4 * half + (e & 3);
-          __builtin_memcpy(vr[e], __builtin_assume_aligned(vb + key * 2 * D + n * NDB * 2, 4 * VW), 4 * VW);
-        }
+          for (int e = 0; e < 8; ++e) {
+            const int key = rb * 32 + 16 * st + (e & 4) * 2 + (e & 3);
+            __builtin_memcpy(vr[e], __builtin_assume_aligned(vb + at + key * 2 * D, 4 * VW), 4 * VW);
+          }
 #pragma unroll
-        for (int db = 0; db < NDB; ++db) {
-          const uint32_t sel = db & 1 ? 0x07060302u : 0x05040100u;
-          const int w = db / 2;
-          const uint4 av = make_uint4(__builtin_amdgcn_perm(vr[1][w], vr[0][w], sel), __builtin_amdgcn_perm(vr[3][w], vr[2][w], sel),
-                                      __builtin_amdgcn_perm(vr[5][w], vr[4][w], sel), __builtin_amdgcn_perm(vr[7][w], vr[6][w], sel));
-          o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(dbf16x8, av), pb, o[db], 0, 0, 0);
+          for (int db = 0; db < NDB; ++db) {
+            const uint32_t sel = db & 1 ? 0x07060302u : 0x05040100u;
+            const int w = db / 2;
+            const uint4 av = make_uint4(__builtin_amdgcn_perm(vr[1][w], vr[0][w], sel), __builtin_amdgcn_perm(vr[3][w], vr[2][w], sel),
+                                        __builtin_amdgcn_perm(vr[5][w], vr[4][w], sel), __builtin_amdgcn_perm(vr[7][w], vr[6][w], sel));
+            o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(dbf16x8, av), pb, o[db], 0, 0, 0);
+          }
         }
       }
+    };
+    // weights below the smallest normal number, which the exponential instruction alone makes
+    // 0, are added by themselves where the tile has any
+    if (__builtin_amdgcn_ballot_w64(fmaf(low, cexp, -off) < -126.f)) {
+      values(std::true_type{});
     }
+    values(std::false_type{});
   };
 
   // One tile of lookahead: before tile t is read, this wave's loads of it are complete and

@@ -85,3 +85,19 @@ def test_dense_at_the_paper_length_65536(causal):
     out = _dense(w, x)
     err = _check_rows(w, x, out, parity.sample_attn_rows(w, 40, seed=5))
     print(f"L=65536 causal={causal}: max row error {err:.3e}")
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("at", [1, 40, 63, 64, 299])
+def test_dense_tiny_weights(d, at):
+    """A weight below the smallest normal number (2^-130) against a value of 2^120, in each part of a
+    tile, for the first and the last queries' waves; the other keys' weights are 0."""
+    q, k, v = (torch.zeros(1, 1, n, d, device="cuda") for n in (200, 300, 300))
+    q[..., 0] = 1
+    k[0, 0, :, 0] = -1e4
+    k[0, 0, 0, 0], k[0, 0, at, 0] = 0, -90.0 * 8
+    v[0, 0, at] = 2.0 ** 120
+    out = tk.attn_dense(q.bfloat16(), k.bfloat16(), v.bfloat16(), 0, False, 0.125).double()
+    want = np.exp(-90.0) * 2.0 ** 120
+    # 2^-130 as a bf16 number: a multiple of 2^-133
+    assert bool(((out - want).abs() <= (2.0 ** -4 + 2.0 ** -8) * want).all()), out.flatten()[0]
