@@ -183,7 +183,8 @@ struct MmArgs {
 
 template <bool TRANS>
 __device__ void cells_fix_row(const MmArgs& a, int y, int64_t bh, int64_t m) {
-  // out row m from its own pairs, by one wave: lanes test 64 entries at a time
+  // out row m from its own pairs, by one wave: lanes test 64 entries at a time. A zero score
+  // gradient (a closed ReLU gate, say) adds nothing to d_Q, whatever its key holds, as by lists.
   const int lane = threadIdx.x & 63;
   const uint16_t* B = (const uint16_t*)a.B[y] + bh * a.head_n;
   uint16_t* out = (uint16_t*)a.out[y] + bh * a.head_m + m * a.d;
@@ -199,7 +200,7 @@ __device__ void cells_fix_row(const MmArgs& a, int y, int64_t bh, int64_t m) {
         const bool in = i < a.off[o + 1];
         const uint32_t e = in ? a.ent[i] : 0u;
         const float v = in ? a.val[y][i] : 0.f;
-        uint64_t hit = __ballot(in && (TRANS ? (e & 63u) : (e >> 6)) == local);
+        uint64_t hit = __ballot(in && (TRANS ? (e & 63u) : (e >> 6)) == local && (TRANS || v != 0.f));
         for (; hit; hit &= hit - 1) {
           const int l = __builtin_ctzll(hit);
           const uint32_t el = (uint32_t)__builtin_amdgcn_readlane((int)e, l);

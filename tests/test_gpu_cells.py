@@ -169,3 +169,26 @@ def test_cells_keep_32_bits(dm):
     assert torch.equal(dw1[:30].float(), (2 * x[0]).expand(30, -1))
     assert torch.equal(dw2[600:630].float(), (2 * g[5]).expand(30, -1))
     assert torch.equal(dx[70].float(), 2 * w1[300])
+
+
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+def test_cells_closed_gate_at_a_key_that_is_not_finite(bad):
+    """A unit whose score is not positive passes no gradient, so its row of W1 does not reach d_X
+    even where it is not finite; a unit with a gradient does; as by lists."""
+    gen = torch.Generator(device="cuda").manual_seed(8)
+    x, g = (torch.randn(200, 256, generator=gen, device="cuda").bfloat16() for _ in range(2))
+    w1, w2 = (torch.randn(500, 256, generator=gen, device="cuda").bfloat16() for _ in range(2))
+    idx = torch.stack([torch.randperm(499, generator=gen, device="cuda")[:40] + 1 for _ in range(200)]).int()
+    dots = torch.randn(200, 40, generator=gen, device="cuda")
+    dots[idx == 7] = -1.0
+    w1[7] = bad
+    got = tk.ffn_backward(x, w1, w2, idx, dots, g)
+    assert int((idx == 7).any(1).sum()) > 0
+    for p, r in zip(got, _lists(lambda: tk.ffn_backward(x, w1, w2, idx, dots, g))):
+        assert torch.isfinite(p).all() and torch.isfinite(r).all()
+        _close(p, r)
+    dots[idx == 7] = 1.0
+    got = tk.ffn_backward(x, w1, w2, idx, dots, g)
+    lst = _lists(lambda: tk.ffn_backward(x, w1, w2, idx, dots, g))
+    assert torch.equal(torch.isfinite(got[0]), torch.isfinite(lst[0]))
+    assert torch.equal((~torch.isfinite(got[0])).all(1), (idx == 7).any(1))
