@@ -195,6 +195,10 @@ __device__ void cells_fix_row(const MmArgs& a, int y, int64_t bh, int64_t m) {
     float s = 0.f;
     for (int c = 0; c < nc; ++c) {
       const int64_t o = TRANS ? (bh * a.nstrip + c) * a.off_row + (m >> 6) : (bh * a.nstrip + (m >> 6)) * a.off_row + c;
+      // the cell's values of the row, one column of the cell per lane, then their sum by column
+      // (a list's order is not fixed)
+      float x = 0.f;
+      uint64_t have = 0;
       for (int32_t i0 = a.off[o]; i0 < a.off[o + 1]; i0 += 64) {
         const int32_t i = i0 + lane;
         const bool in = i < a.off[o + 1];
@@ -205,9 +209,15 @@ __device__ void cells_fix_row(const MmArgs& a, int y, int64_t bh, int64_t m) {
           const int l = __builtin_ctzll(hit);
           const uint32_t el = (uint32_t)__builtin_amdgcn_readlane((int)e, l);
           const float vl = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
-          const int64_t n = (int64_t)c * 64 + (TRANS ? (el >> 6) : (el & 63u));
-          s = fmaf(vl, load_elem<uint16_t>(B, n * a.d + col), s);
+          const int at = (int)(TRANS ? (el >> 6) : (el & 63u));
+          if (lane == at) x += vl;
+          have |= uint64_t(1) << at;
         }
+      }
+      for (; have; have &= have - 1) {
+        const int at = __builtin_ctzll(have);
+        const float xl = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), at));
+        s = fmaf(xl, load_elem<uint16_t>(B, ((int64_t)c * 64 + at) * a.d + col), s);
       }
     }
     if (c0 + lane < a.d) store_elem<uint16_t>(out, c0 + lane, s);

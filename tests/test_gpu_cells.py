@@ -192,3 +192,29 @@ def test_cells_closed_gate_at_a_key_that_is_not_finite(bad):
     lst = _lists(lambda: tk.ffn_backward(x, w1, w2, idx, dots, g))
     assert torch.equal(torch.isfinite(got[0]), torch.isfinite(lst[0]))
     assert torch.equal((~torch.isfinite(got[0])).all(1), (idx == 7).any(1))
+
+
+def _same_bits(a, b):
+    """Equal bit for bit (a NaN's bits included)."""
+    return torch.equal(a.view(torch.int16), b.view(torch.int16))
+
+
+@pytest.mark.parametrize("N,dff", [(400, 1000), (140, 4000)])  # whole products, split products
+def test_cells_rows_not_finite_repeat(N, dff):
+    """Rows computed again because of one column that is not finite: the other columns' sums are the
+    same in every call, and near the lists'."""
+    gen = torch.Generator(device="cuda").manual_seed(9)
+    x, g = (torch.randn(N, 256, generator=gen, device="cuda").bfloat16() for _ in range(2))
+    w1, w2 = (torch.randn(dff, 256, generator=gen, device="cuda").bfloat16() for _ in range(2))
+    _, idx, dots = tk.ffn(x, w1, w2, 100, cache=True)
+    w1[:, 3], x[:, 5] = float("inf"), float("inf")
+    got = tk.ffn_backward(x, w1, w2, idx, dots, g)
+    for _ in range(5):
+        for p, q in zip(got, tk.ffn_backward(x, w1, w2, idx, dots, g)):
+            assert _same_bits(p, q)
+    lst = _lists(lambda: tk.ffn_backward(x, w1, w2, idx, dots, g))
+    used = torch.zeros(dff, dtype=torch.bool, device="cuda").index_fill_(0, idx.flatten().long(), True)
+    assert not torch.isfinite(got[0][:, 3]).any() and not torch.isfinite(got[1][used, 5]).any()
+    for p, r, c in zip(got, lst, (3, 5, 0)):
+        keep = torch.arange(256, device="cuda") != c
+        _close(p[:, keep], r[:, keep])
