@@ -38,8 +38,8 @@ namespace topk {
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 // One workgroup per strip; cells <= CELL_MAX (one thread each in the scan). A strip in which
-// a row lists a key twice is marked (after its ranges): the bf16 products then add that
-// strip's entries one by one instead of storing them side by side.
+// a row lists a key twice is marked (after its ranges), and its lists are in pair order: the
+// products then add its entries one by one instead of storing them side by side.
 __global__ __launch_bounds__(1024) void k_cells_build(BwdProblem bp, CellBufs cb) {
   extern __shared__ uint32_t seen[];  // cb.seen words: a bit per (row, key) of the strip
   __shared__ uint32_t cnt[CELL_MAX];
@@ -60,7 +60,10 @@ __global__ __launch_bounds__(1024) void k_cells_build(BwdProblem bp, CellBufs cb
 #pragma unroll 4
   for (uint32_t e = tid; e < n; e += 1024) {
     const int32_t j = idx[e];
-    if (valid(j)) atomicAdd(&cnt[j >> 6], 1u);
+    if (!valid(j)) continue;
+    atomicAdd(&cnt[j >> 6], 1u);
+    const uint32_t bit = e / k * (uint32_t)cb.ncell * 64u + (uint32_t)j;
+    if (atomicOr(&seen[bit >> 5], 1u << (bit & 31u)) >> (bit & 31u) & 1u) repeated = 1;
   }
   // the softmax's maximum and normaliser of each row, over its cached scores, 16 lanes a row
   const int sr = tid >> 4, sl = tid & 15;
@@ -95,20 +98,38 @@ __global__ __launch_bounds__(1024) void k_cells_build(BwdProblem bp, CellBufs cb
     if (tid == cb.ncell - 1) off[cb.ncell] = (int32_t)(beg + c);
   }
   __syncthreads();
-#pragma unroll 4
-  for (uint32_t e = tid; e < n; e += 1024) {
-    const int32_t j = idx[e];
-    if (!valid(j)) continue;
-    const uint32_t r = e / k, pos = atomicAdd(&cnt[j >> 6], 1u);
-    {
-      const uint32_t bit = r * (uint32_t)cb.ncell * 64u + (uint32_t)j;
-      if (atomicOr(&seen[bit >> 5], 1u << (bit & 31u)) >> (bit & 31u) & 1u) repeated = 1;
-    }
+  auto store = [&](uint32_t pos, uint32_t e, int32_t j) {
+    const uint32_t r = e / k;
     const float s = dots[e];
     cb.ent[pos] = r << 6 | ((uint32_t)j & 63u);
     cb.w[pos] = bp.act == ACT_SOFTMAX ? __expf(bp.scale * (s - mx_lds[r])) * inv_lds[r] : fmaxf(s, 0.f);
+  };
+  if (!repeated) {
+#pragma unroll 4
+    for (uint32_t e = tid; e < n; e += 1024) {
+      const int32_t j = idx[e];
+      if (valid(j)) store(atomicAdd(&cnt[j >> 6], 1u), e, j);
+    }
+  } else if (wave == 0) {  // in pair order: 64 pairs at a time, lanes of one cell by rank
+    for (uint32_t e0 = 0; e0 < n; e0 += 64) {
+      const uint32_t e = e0 + lane;
+      const int32_t j = e < n ? idx[e] : -1;
+      const bool ok = valid(j);
+      const uint32_t cell = ok ? (uint32_t)j >> 6 : 0u;
+      uint64_t peers = __ballot(ok);
+#pragma unroll
+      for (int t = 0; t < 8; ++t) {  // (CELL_MAX is 2^8)
+        const bool bit = cell >> t & 1u;
+        const uint64_t m = __ballot(bit);
+        peers &= bit ? m : ~m;
+      }
+      const uint32_t rank = lanes_below(peers), first = ok ? cnt[cell] : 0u;
+      wave_sync_lds();
+      if (ok && rank == 0) cnt[cell] = first + (uint32_t)__popcll(peers);
+      wave_sync_lds();
+      if (ok) store(first + rank, e, j);
+    }
   }
-  __syncthreads();
   if (tid == 0) off[cb.ncell + 1] = (int32_t)repeated;
 }
 
@@ -376,12 +397,12 @@ __global__ __launch_bounds__(256, 2) void k_cells_mm(MmArgs a) {
           for (int u = 0; u < 4; ++u)
             if (e[u] != 0xFFFFFFFFu) put(cur, e[u], v[u]);
         }
-      } else if (tid == 0) {  // one thread adds the entries in turn
+      } else if (tid < 128) {  // each thread adds its row's entries, in the lists' order
         for (int i = 0; i < n0 + n1; ++i) {
           uint32_t e;
           float v;
           fetch(i, e, v);
-          cur[place(e)] += v;
+          if ((int)((TRANS ? e & 63u : e >> 6 & 63u) + (e >> 12 << 6)) == tid) cur[place(e)] += v;
         }
       }
       lds_barrier();  // the tile is complete; every wave is done with the other one

@@ -218,3 +218,21 @@ def test_cells_rows_not_finite_repeat(N, dff):
     for p, r, c in zip(got, lst, (3, 5, 0)):
         keep = torch.arange(256, device="cuda") != c
         _close(p[:, keep], r[:, keep])
+
+
+@pytest.mark.parametrize("N,dff", [(300, 500), (140, 4000)])  # whole products, split products
+def test_cells_keys_listed_often_repeat(N, dff):
+    """Keys listed many times in a row: their sums run in pair order, so every call gives the same
+    bits; near the lists'."""
+    gen = torch.Generator(device="cuda").manual_seed(10)
+    x, g = (torch.randn(N, 256, generator=gen, device="cuda").bfloat16() for _ in range(2))
+    w1, w2 = (torch.randn(dff, 256, generator=gen, device="cuda").bfloat16() for _ in range(2))
+    idx = torch.randint(-1, 30, (N, 100), generator=gen, device="cuda", dtype=torch.int32)
+    idx[:, 50:] += dff - 30
+    dots = torch.randn(N, 100, generator=gen, device="cuda")
+    got = tk.ffn_backward(x, w1, w2, idx, dots, g)
+    for _ in range(5):
+        for p, q in zip(got, tk.ffn_backward(x, w1, w2, idx, dots, g)):
+            assert torch.equal(p, q)
+    for p, r in zip(got, _lists(lambda: tk.ffn_backward(x, w1, w2, idx, dots, g))):
+        _close(p, r)
