@@ -251,6 +251,9 @@ __global__ __launch_bounds__(256, 2) void k_cells_mm(MmArgs a) {
   constexpr int RT = 8 / WR;       // 16-row tiles per wave
   // the sparse operand of two cells in turn, in 32 bits
   constexpr int TS = 68, TILE = 128 * TS;  // row stride, elements per tile
+  // its values 2^16 times as large (exactly; undone at the end), so that the last bit of any
+  // float, 2^-149, is one that the last of its three bf16 numbers can hold
+  constexpr float UP = 65536.f;
   __shared__ __attribute__((aligned(16))) float tiles[2][TILE];
   __shared__ int bad_lds[128];
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, n = lane & 15,
@@ -342,7 +345,7 @@ __global__ __launch_bounds__(256, 2) void k_cells_mm(MmArgs a) {
       const uint32_t r = e >> 6 & 63u, k = e & 63u, h = e >> 12 << 6;
       return TRANS ? (k + h) * TS + r : (r + h) * TS + k;
     };
-    auto put = [&](float* t, uint32_t e, float v) { t[place(e)] = v; };
+    auto put = [&](float* t, uint32_t e, float v) { t[place(e)] = v * UP; };
     auto clear = [&](float* t, uint32_t e) { t[place(e)] = 0.f; };
     uint64_t todo = __ballot(ln0 + ln1 > 0);
     const uint64_t rep = __ballot(lrep != 0);  // cells with keys listed twice in a row
@@ -402,7 +405,7 @@ __global__ __launch_bounds__(256, 2) void k_cells_mm(MmArgs a) {
           uint32_t e;
           float v;
           fetch(i, e, v);
-          if ((int)((TRANS ? e & 63u : e >> 6 & 63u) + (e >> 12 << 6)) == tid) cur[place(e)] += v;
+          if ((int)((TRANS ? e & 63u : e >> 6 & 63u) + (e >> 12 << 6)) == tid) cur[place(e)] += v * UP;
         }
       }
       lds_barrier();  // the tile is complete; every wave is done with the other one
@@ -465,6 +468,10 @@ __global__ __launch_bounds__(256, 2) void k_cells_mm(MmArgs a) {
       lds_barrier();  // the other tile is clear: the next cell's entries may go there
     }
   }
+#pragma unroll
+  for (int r = 0; r < RT; ++r)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) acc[r][c] *= 1.f / UP;
   // lane: rows 4 g + v of row tile r, columns col0 .. col0 + 3
   if (a.nsplit > 1) {
     float* part = a.part + ((int64_t)sp * a.which + y) * a.BH * a.M * a.d;

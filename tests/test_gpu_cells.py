@@ -169,6 +169,12 @@ def test_cells_keep_32_bits(dm):
     assert torch.equal(dw1[:30].float(), (2 * x[0]).expand(30, -1))
     assert torch.equal(dw2[600:630].float(), (2 * g[5]).expand(30, -1))
     assert torch.equal(dx[70].float(), 2 * w1[300])
+    # weights as small as floats get (multiples of 2^-149)
+    g[5] *= 2.0 ** 100
+    g[290] = -g[5]
+    dots[5], dots[290] = dots[5] * 2.0 ** -100 * 2.0 ** -49, dots[290] * 2.0 ** -100 * 2.0 ** -49
+    dw2 = tk.ffn_backward(*(t.bfloat16() for t in (x, w1, w2)), idx, dots, g.bfloat16())[2]
+    assert torch.equal(dw2[600:630].double(), (2.0 ** -148 * g[5].double()).expand(30, -1))
 
 
 @pytest.mark.parametrize("bad", [float("inf"), float("nan")])
