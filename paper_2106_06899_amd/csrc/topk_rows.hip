@@ -50,6 +50,7 @@ struct RowsArgs {
   const void* V;
   void* out;
   int64_t Lq, tiles_per_head, kv_head_stride;
+  int64_t first;        // first workgroup of this launch
   int Lk, k, causal, act;
   float c;              // softmax: scale * log2(e)
   int32_t* idx_out;
@@ -117,7 +118,7 @@ __global__ __launch_bounds__(64 * E, 4) void k_rows(RowsArgs a) {
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // consecutive row tiles of a head on one XCD (its L2 holds the head's keys and values)
   const int64_t NGR = gridDim.x, bid = blockIdx.x;
-  const int64_t wg = (NGR % 8 == 0) ? (bid % 8) * (NGR / 8) + bid / 8 : bid;
+  const int64_t wg = a.first + ((NGR % 8 == 0) ? (bid % 8) * (NGR / 8) + bid / 8 : bid);
   const int64_t bh = wg / a.tiles_per_head, i0 = (wg - bh * a.tiles_per_head) * TR;
   const T* Qt = (const T*)a.Q + (bh * a.Lq + i0) * D;
   const T* Kh = (const T*)a.K + bh * a.kv_head_stride;
@@ -497,12 +498,17 @@ __global__ __launch_bounds__(64 * E, 4) void k_rows(RowsArgs a) {
 }
 
 template <typename T, int D, int E, int TR>
-hipError_t launch_rows_inst(const RowsArgs& a, int64_t BH, hipStream_t st) {
+hipError_t launch_rows_inst(RowsArgs a, int64_t BH, hipStream_t st) {
   const size_t sh = (size_t)TR * (64 * E + 4) * 4 + (size_t)E * a.scratch * 8;
   const int64_t grid = BH * a.tiles_per_head;
-  if (grid > 0x7FFFFFFF) return hipErrorInvalidValue;
-  k_rows<T, D, E, TR><<<(unsigned)grid, 64 * E, sh, st>>>(a);
-  return hipGetLastError();
+  constexpr int64_t most = (int64_t(1) << 32) / (64 * E) - 8;  // a launch has fewer than 2^32 threads
+  hipError_t e = hipSuccess;
+  for (a.first = 0; a.first < grid && e == hipSuccess; a.first += most) {
+    const int64_t left = grid - a.first;
+    k_rows<T, D, E, TR><<<(unsigned)(left < most ? left : most), 64 * E, sh, st>>>(a);
+    e = hipGetLastError();
+  }
+  return e;
 }
 
 template <typename T, int D>
@@ -527,7 +533,7 @@ hipError_t launch_rows(const Problem& pb, hipStream_t st) {
   a.V = pb.V;
   a.out = pb.out;
   a.Lq = pb.Lq;
-  a.tiles_per_head = 0;
+  a.tiles_per_head = a.first = 0;
   a.kv_head_stride = pb.kv_head_stride;
   a.Lk = (int)pb.Lk;
   a.k = (int)pb.k;

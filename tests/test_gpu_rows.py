@@ -121,3 +121,14 @@ def test_short_rows_tiny_weights(Lk, k, dtype):
     # the weight has 19 bits; its exponent, 130, an error of 2^-17 at most
     tol = 2.0 ** -16 + (2.0 ** -8 if dtype == torch.bfloat16 else 0)
     assert bool(((out - want).abs() <= tol * want).all()), out.flatten()[0]
+
+
+def test_short_rows_beyond_one_launch():
+    """More workgroups than one launch can hold (2^32 threads): 2^24 and some heads of one key."""
+    B, H = 4096, 4104
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    q = torch.ones(B, H, 1, 32, device="cuda", dtype=torch.bfloat16)
+    v = torch.empty_like(q)
+    for b in range(0, B, 512):
+        v[b:b + 512] = torch.randn(512, H, 1, 32, generator=gen, device="cuda")
+    assert torch.equal(tk.attn(q, q, v, 1), v)
