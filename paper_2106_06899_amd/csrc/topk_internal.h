@@ -229,6 +229,10 @@ hipError_t launch_backward_cells(const BwdProblem& bp, const CellBufs& cb, hipSt
 // 48 heads of 1024, 16: 264 / 195; 12 heads of 2048, 16: 196 / 210.
 inline bool cells_ok(const BwdProblem& bp) {
   if (bp.list_mode != 0 || bp.dtype != T_BF16 || bp.d % 32 != 0 || bp.Lk > (int64_t)64 * CELL_MAX) return false;
+  // every launch below 2^32 threads: 1024 a strip; 256 a tile of the products, whose column
+  // tiles (at most four) and two sides make eight at most
+  const int64_t tq = (bp.Lq + 127) / 128, tk = (bp.Lk + 127) / 128;
+  if (bp.BH * ((bp.Lq + 63) / 64) >= 1 << 22 || bp.BH * (tq > tk ? tq : tk) * 8 >= 1 << 24 || bp.BH * tq * tk >= 1 << 24) return false;
   if (bp.d >= 256) return bp.Lk <= 40 * bp.k;
   const int64_t tiles = bp.BH * ((bp.Lq + 127) / 128);
   if (bp.d >= 128) return bp.Lk <= 16 * bp.k && tiles >= 128;

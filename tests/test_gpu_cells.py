@@ -242,3 +242,14 @@ def test_cells_keys_listed_often_repeat(N, dff):
             assert torch.equal(p, q)
     for p, r in zip(got, _lists(lambda: tk.ffn_backward(x, w1, w2, idx, dots, g))):
         _close(p, r)
+
+
+def test_cells_leave_more_strips_than_a_launch_holds_to_the_lists():
+    """2^22 heads of one row are more strips of 1024 threads than a launch can hold. One key per row:
+    its weight is 1, whatever its score."""
+    B, H = 2048, 2052
+    q = torch.ones(B, H, 1, 64, device="cuda", dtype=torch.bfloat16)
+    g = torch.randn(B, H, 1, 64, generator=torch.Generator(device="cuda").manual_seed(2), device="cuda").bfloat16()
+    idx = torch.zeros(B, H, 1, 1, dtype=torch.int32, device="cuda")
+    dq, dk, dv = tk.attn_backward(q, q, q, idx, idx.float(), g)
+    assert torch.equal(dv, g) and not dq.any() and not dk.any()
