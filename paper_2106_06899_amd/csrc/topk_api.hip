@@ -75,7 +75,8 @@ enum Path { PATH_FUSED = 1, PATH_TILE = 2, PATH_FILTER = 4 };
 
 struct Plan {
   int path;
-  bool few;  // PATH_TILE by the few-query kernels
+  bool few;        // PATH_TILE by the few-query kernels,
+  bool few_whole;  // all of a head's queries in one chunk
   ScanCfg scan;
   int64_t nchunk, total_chunks, per_pass;
   size_t per_chunk, fixed;
@@ -137,9 +138,10 @@ bool filter_ok(const Problem& pb) {
 // candidates kept per (row, half) of the list buffers
 int64_t caph_for(const Problem& pb, int path) { return path == PATH_FILTER && pb.k > 256 ? 2 * FUSED_CAPH : FUSED_CAPH; }
 
-// Few queries per head (bf16): the scores of all its queries in workspace, whatever the
-// chunk size (at most 128 rows of 65536 scores, less than the fallback rows that the
-// fused and filtered paths keep). k up to 512 and, so that the block maxima's bound is a
+// Few queries per head (bf16), by shape alone, so that the chunk size changes no result. In
+// place of the fused and filtered paths the scores of all of a head's queries are in
+// workspace, whatever the chunk size (at most 128 rows of 65536 scores, less than the fallback
+// rows those keep); in place of the chunk-tile path those of a chunk, as there. k up to 512 and, so that the block maxima's bound is a
 // sharp one, at least five blocks of 16 keys per four kept. The scan takes as long for 1 as
 // for 256 queries of a head (0.7 us per 64 keys at d = 64, 1.3 at d = 128); writing the
 // scores takes 1 us per 10^6, so 8192 rows in all are where the two meet. The filtered and
@@ -151,7 +153,7 @@ int64_t caph_for(const Problem& pb, int path) { return path == PATH_FILTER && pb
 bool few_ok(const Problem& pb, int path) {
   return pb.dtype == T_BF16 && pb.d % 32 == 0 && !pb.causal && !pb.tile_only && pb.Lq <= FEW_ROWS && pb.q0 == 0 &&
          pb.q1 == pb.Lq && pb.Lk > ROWS_MAX_LK && pb.Lk <= 65536 && pb.k <= 512 && 4 * ((pb.Lk + 15) / 16) >= 5 * pb.k &&
-         (path != PATH_TILE || pb.C >= pb.Lq) && pb.BH * pb.Lq <= (path == PATH_FUSED ? 8192 : 2048);
+         pb.BH * pb.Lq <= (path == PATH_FUSED ? 8192 : 2048);
 }
 
 void choose_long_path(const Problem& pb, Plan* pl) {
@@ -193,12 +195,13 @@ void choose_long_path(const Problem& pb, Plan* pl) {
 void choose_path(const Problem& pb, Plan* pl) {
   choose_long_path(pb, pl);
   pl->few = few_ok(pb, pl->path);
+  pl->few_whole = pl->few && pl->path != PATH_TILE;
   if (pl->few) pl->path = PATH_TILE;
 }
 // the path, and the problem as that path runs it
 void choose_path_for(Problem* pb, Plan* pl) {
   choose_path(*pb, pl);
-  if (pl->few) pb->C = pb->Lq;
+  if (pl->few_whole) pb->C = pb->Lq;
 }
 
 size_t row_bytes(const Problem& pb, const Plan& pl) {
@@ -333,7 +336,13 @@ int run(Problem whole, hipStream_t st, bool report, void* fixed_ws = nullptr, si
   for (int q = 0; q < np; ++q) {
     choose_path_for(&parts[q], &plans[q]);
     plan_sizes(parts[q], &plans[q], budget);
-    const size_t n = plan_total(plans[q], parts[q]);
+    size_t n = plan_total(plans[q], parts[q]);
+    if (ws_given && n > ws_given_bytes && plans[q].few && !plans[q].few_whole) {
+      // a workspace that holds a chunk's scores, but not their block maxima as well
+      plans[q].few = false;
+      plan_sizes(parts[q], &plans[q], budget);
+      n = plan_total(plans[q], parts[q]);
+    }
     need = n > need ? n : need;
   }
   char* ws = (char*)ws_given;

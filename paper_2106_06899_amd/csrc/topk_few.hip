@@ -24,18 +24,19 @@ __global__ __launch_bounds__(256, RT <= 2 ? 4 : 2) void k_few_scores(Problem pb,
   constexpr int NS = 16 / KT;  // 32-feature steps whose keys are in flight together
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n = lane & 15, g = lane >> 4;
   if (blockIdx.x == 0 && threadIdx.x == 0) *bufs.redo_count = 0;  // for the select
-  // key ranges fastest (consecutive ones on one XCD), then groups of 16 RT queries, then heads
+  // key ranges fastest (consecutive ones on one XCD), then groups of 16 RT queries, then chunks
   const int64_t NG = gridDim.x, bid = blockIdx.x;
   int64_t wg = (NG % 8 == 0) ? (bid % 8) * (NG / 8) + bid / 8 : bid;
-  const int64_t nk = (pb.Lk + 64 * KT - 1) / (64 * KT), nq = (pb.Lq + 16 * RT - 1) / (16 * RT);
+  const int64_t nk = (pb.Lk + 64 * KT - 1) / (64 * KT), nq = (pb.C + 16 * RT - 1) / (16 * RT);
   const int64_t key0 = (wg % nk) * (64 * KT) + wave * (16 * KT);
   wg /= nk;
   const int r0 = (int)(wg % nq) * 16 * RT;
-  const int64_t cl = wg / nq, bh = ps.c0 + cl;  // one chunk per head
-  if (key0 >= pb.Lk) return;
+  const int64_t cl = wg / nq, id = ps.c0 + cl, bh = id / ps.nchunk, i0 = (id - bh * ps.nchunk) * pb.C;
+  const int rows = (int)(pb.Lq - i0 < pb.C ? pb.Lq - i0 : pb.C);  // the chunk's
+  if (key0 >= pb.Lk || r0 >= rows) return;
   const uint16_t* Kh = (const uint16_t*)pb.K + bh * pb.kv_head_stride + key0 * pb.d;
-  const uint16_t* Qh = (const uint16_t*)pb.Q + bh * pb.Lq * pb.d;
-  const int d = (int)pb.d, left = (int)(pb.Lk - key0 < 16 * KT ? pb.Lk - key0 : 16 * KT), rows = (int)pb.Lq;
+  const uint16_t* Qh = (const uint16_t*)pb.Q + (bh * pb.Lq + i0) * pb.d;
+  const int d = (int)pb.d, left = (int)(pb.Lk - key0 < 16 * KT ? pb.Lk - key0 : 16 * KT);
   uint32_t ko[KT], qo[RT];
 #pragma unroll
   for (int t = 0; t < KT; ++t) ko[t] = (uint32_t)(min(16 * t + n, left - 1) * d + 8 * g);  // past the end: the last key
@@ -196,14 +197,14 @@ __global__ __launch_bounds__(64) void k_few_select(Problem pb, Pass ps, PassBufs
 }
 
 hipError_t launch_few_scores(const Problem& pb, const Pass& ps, const PassBufs& b, hipStream_t st) {
-  const int RT = pb.Lq <= 16 ? 1 : pb.Lq <= 32 ? 2 : 4;
-  const int64_t nq = (pb.Lq + 16 * RT - 1) / (16 * RT) * ps.nc;
+  const int RT = pb.C <= 16 ? 1 : pb.C <= 32 ? 2 : 4;
+  const int64_t nq = (pb.C + 16 * RT - 1) / (16 * RT) * ps.nc;
   // 64 keys a wave, or 16 (more of their features in flight) where that would leave fewer
   // than two waves a CU: 24 tokens, d_model 768, d_ff 16384 (256 or 1024 waves) 24 -> 16 us;
   // 8 tokens, 1024, 65536 (1024 or 4096 waves) 30 -> 33 us
   const int KT = (pb.Lk + 63) / 64 * nq < 512 ? 1 : 4;
   const int64_t g = ((pb.Lk + 64 * KT - 1) / (64 * KT)) * nq;
-  if (g > 0x7FFFFFFF || pb.dtype != T_BF16 || pb.d % 32 != 0 || ps.nchunk != 1 || pb.C < pb.Lq || !b.blk) return hipErrorInvalidValue;
+  if (g > 0x7FFFFFFF || pb.dtype != T_BF16 || pb.d % 32 != 0 || !b.blk) return hipErrorInvalidValue;
 #define TOPK_FEW(RT_)                                                                 \
   do {                                                                                \
     if (KT == 1) k_few_scores<RT_, 1><<<(unsigned)g, 256, 0, st>>>(pb, ps, b);        \

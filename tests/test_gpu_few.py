@@ -85,3 +85,31 @@ def test_finalize_of_few_rows(kw):
     out, idx, _ = parity.run_ffn(w, x)
     parity.check_ffn(w, x, out, idx)
     assert torch.equal(parity.run_ffn(w, x, debug=False), out)
+
+
+@pytest.mark.parametrize("Lk,d,k", [(1800, 64, 85), (1030, 96, 40), (2048, 160, 64), (1999, 128, 90)])
+def test_few_queries_in_chunks_of_the_tile_path(Lk, d, k):
+    """Where they take the place of the chunk-tile path the kernels run chunk by chunk: the same kernel
+    whatever the chunk size (its workspace holds the block maxima), and the same bits; in a workspace
+    too small for the maxima, the chunk-tile path's own kernels."""
+    w = wl.WORKLOADS["c2"].scaled(B=2, H=3, Lq=100, Lk=Lk, d=d, k=k, chunk=128, scale=float(np.float32(d ** -0.5)))
+    x = wl.make_inputs(w)
+    ref = parity.run_attn(w, x)
+    parity.check_attn(w, x, ref[0], ref[1], rows=parity.sample_attn_rows(w, 60, seed=3))
+    for C in (1, 7, 33, 64, 100):
+        print("[case] chunk", C, w, flush=True)
+        assert tk.attn_workspace_bytes(w.B, w.H, w.Lq, Lk, d, k, C) >= w.B * w.H * w.Lq * ((Lk + 15) // 16 * 68 + 8 * k)
+        for a, b in zip(ref, parity.run_attn(w, x, chunk=C)):
+            assert torch.equal(a, b)
+    q, kk, v = (parity.to_dev(x[n]) for n in ("Q", "K", "V"))
+    got = torch.empty_like(q)
+    size = 100 * (4 * Lk + 8 * k + 4) + 8 * 256  # one chunk of the chunk-tile path
+    ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+    tk._raise(tk.lib().topk_set_workspace(ws.data_ptr(), size))
+    try:
+        tk._raise(tk.lib().topk_attn(q.data_ptr(), kk.data_ptr(), v.data_ptr(), got.data_ptr(), w.B, w.H, w.Lq, Lk, d, k, 100, 0,
+                                     w.scale, tk.TOPK_BF16, torch.cuda.current_stream().cuda_stream))
+        torch.cuda.synchronize()
+    finally:
+        tk.lib().topk_set_workspace(None, 0)
+    parity.check_attn(w, x, got, ref[1], rows=parity.sample_attn_rows(w, 60, seed=3))
