@@ -2032,12 +2032,19 @@ hipError_t launch_tile_scores(const Problem& pb, const Pass& ps, const PassBufs&
     k_tile_scores_mfma<0><<<(unsigned)g, 256, 0, st>>>(pb, ps, b);
     return hipGetLastError();
   }
-  // 16-byte loads of whole groups of 16 features; a one-dimensional grid (256 threads each, below
-  // 2^32 in all). Other rows and types keep the scalar kernel.
-  const int64_t g = ((pb.Lk + 63) / 64) * ((pb.C + 127) / 128) * ps.nc;
-  if (pb.dtype == T_F32 && pb.d % 16 == 0 && g < (1 << 24)) {
-    k_tile_scores_f32<<<(unsigned)g, 256, 0, st>>>(pb, ps, b.scores);
-    return hipGetLastError();
+  // 16-byte loads of whole groups of 16 features. Other rows and types keep the scalar kernel: by type
+  // and feature size alone, so that the chunk size changes no score. A launch has fewer than 2^32
+  // threads, 256 a tile: as many chunks each as that allows (one always does).
+  if (pb.dtype == T_F32 && pb.d % 16 == 0) {
+    const int64_t tiles = ((pb.Lk + 63) / 64) * ((pb.C + 127) / 128), most = ((1 << 24) - 1) / tiles;
+    if (most < 1) return hipErrorInvalidValue;
+    hipError_t e = hipSuccess;
+    for (int64_t n0 = 0; n0 < ps.nc && e == hipSuccess; n0 += most) {
+      const int64_t n = ps.nc - n0 < most ? ps.nc - n0 : most;
+      k_tile_scores_f32<<<(unsigned)(tiles * n), 256, 0, st>>>(pb, Pass{ps.c0 + n0, n, ps.nchunk}, b.scores + n0 * pb.C * pb.Lk);
+      e = hipGetLastError();
+    }
+    return e;
   }
   dim3 grid((unsigned)((pb.Lk + 63) / 64), (unsigned)((pb.C + 63) / 64), (unsigned)ps.nc);
   if (pb.dtype == T_BF16)

@@ -4,6 +4,7 @@ steps and the diagonal, and the same bits whatever the chunk."""
 import pytest
 import torch
 
+import paper_2106_06899_amd as tk
 from paper_2106_06899_amd import workloads as wl
 from tests import parity
 
@@ -27,3 +28,13 @@ def test_fp32_score_tiles(case):
     parity.check_attn(w, x, out, idx, rows=parity.sample_attn_rows(w, min(300, H * Lq), seed=6))
     other = parity.run_attn(w.scaled(chunk=50), x, debug=False)
     assert torch.equal(other, out)
+
+
+def test_fp32_scores_of_many_chunks():
+    """Chunks of one row in such numbers that one launch cannot hold their tiles: the same scores, bit
+    for bit, as in chunks of 1024."""
+    gen = torch.Generator(device="cuda").manual_seed(2)
+    q, k = torch.randn(1, 1, 60000, 48, generator=gen, device="cuda"), torch.randn(1, 1, 20000, 48, generator=gen, device="cuda")
+    ref = tk.attn(q, k, k, 8, 1024, cache=True)
+    for a, b in zip(ref, tk.attn(q, k, k, 8, 1, cache=True)):
+        assert torch.equal(a, b)
