@@ -774,8 +774,9 @@ int topk_scan_ablation(const void* Q, const void* K, int64_t B, int64_t H, int64
   int rc = attn_problem(&pb, Q, K, K, (void*)Q, B, H, Lq, Lk, d, k, chunk, 0, 1.f, TOPK_BF16, nullptr, nullptr, true);
   if (rc) return rc;
   Plan pl;
-  choose_path(pb, &pl);
-  if (pl.path != PATH_FUSED || pl.scan.mode != MODE_SAMPLE || pb.d != 64 || pl.scan.union_rank != 20)
+  choose_long_path(pb, &pl);  // the scan also where a call of a few queries would not take it
+  pl.few = pl.few_whole = false;
+  if (pl.path != PATH_FUSED || pb.d != 64 || pl.scan.union_rank != 20)
     return fail(TOPK_E_UNSUPPORTED, "the scan ablation runs on the sampled fused path with d = 64, 32 < k <= 64");
   pl.scan.score_only = score_only ? 1 : 0;
   plan_sizes(pb, &pl, g_budget.load(std::memory_order_relaxed));

@@ -113,3 +113,13 @@ def test_few_queries_in_chunks_of_the_tile_path(Lk, d, k):
     finally:
         tk.lib().topk_set_workspace(None, 0)
     parity.check_attn(w, x, got, ref[1], rows=parity.sample_attn_rows(w, 60, seed=3))
+
+
+@pytest.mark.parametrize("score_only", [False, True])
+def test_scan_ablation_of_few_queries(score_only):
+    """The measurement hook times the scan at any number of queries."""
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    q, k = (torch.randn(1, 4, n, 64, generator=gen, device="cuda").bfloat16() for n in (100, 20000))
+    tk.profile_begin()
+    tk.scan_ablation(q, k, 64, score_only=score_only)
+    assert tk.profile_end()["score"][1] == 1
