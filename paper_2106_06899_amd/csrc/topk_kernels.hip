@@ -154,15 +154,15 @@ __global__ __launch_bounds__(256, 3) void k_tile_scores_f32(Problem pb, Pass ps,
   }
   // Lane: query n of block b, keys 4 g .. 4 g + 3 of block a. Through LDS, so that each store
   // is one query's 64 keys side by side (a row of the tile need not start at 16 bytes).
-  __shared__ float stash[4][16 * 68];
+  __shared__ __attribute__((aligned(16))) float stash[4][16 * 68];
   float* sw = stash[wave];
   const int64_t key = key0 + lane;
 #pragma unroll
   for (int b = 0; b < 2; ++b) {
-    __builtin_amdgcn_wave_barrier();
+    wave_sync_lds();
 #pragma unroll
     for (int a = 0; a < 4; ++a) *(f32x4*)(sw + n * 68 + 16 * a + 4 * g) = acc[a][b];
-    __builtin_amdgcn_wave_barrier();
+    wave_sync_lds();
     for (int r = 0; r < 16; ++r) {
       const int64_t lr = r0 + 16 * b + r, i = i0 + lr;
       if (lr >= pb.C || i >= pb.q1) break;
