@@ -211,7 +211,8 @@ const char* topk_last_error(void);
 /*
  * Which implementation the arguments select (rows of at most 1024 keys, k <= 256 and
  * d = 32, 64, 96 or 128 run as one kernel that keeps a row's scores in LDS and uses no
- * workspace, reported as the path longer rows of their kind take): 1 = fused score+filter path
+ * workspace, reported as the path longer rows of their kind take; except at most eight bf16
+ * queries per head against more than 200 MB of keys and values, which run as path 2): 1 = fused score+filter path
  * (bf16 MFMA score tiles, candidates filtered on chip), 2 = chunk-tile path
  * (the chunk's score tile in workspace, then a row-wise select), 3 = both, by rows
  * (causal masks on the fused path: the first 1024 R rows of every head, whose few

@@ -149,11 +149,13 @@ int64_t caph_for(const Problem& pb, int path) { return path == PATH_FILTER && pb
 // Measured (us, before / now): 64 heads x 5 queries, 20001 keys, d 128, k 128: 442 / 103; 8 x
 // 1, 60000, d 64: 714 / 40; 64 x 64, 20001, d 64: 458 / 169; 128 x 64, 4096, d 64: 107 / 97; 256
 // x 128, 2048, d 64 (tiled): 195 / 228; 64 x 128, 9000, d 96 (filtered): 167 / 191; feed-forward
-// 24 tokens, 768, 16384 units, k 256: 115 / 41; 128, 1024, 32768, k 512: 140 / 98.
+// 24 tokens, 768, 16384 units, k 256: 115 / 41; 128, 1024, 32768, k 512: 140 / 98. Heads of at
+// most 1024 keys: where the short-row kernel would read more than the caches hold (rows_few).
 bool few_ok(const Problem& pb, int path) {
   return pb.dtype == T_BF16 && pb.d % 32 == 0 && !pb.causal && !pb.tile_only && pb.Lq <= FEW_ROWS && pb.q0 == 0 &&
-         pb.q1 == pb.Lq && pb.Lk > ROWS_MAX_LK && pb.Lk <= 65536 && pb.k <= 512 && 4 * ((pb.Lk + 15) / 16) >= 5 * pb.k &&
-         pb.BH * pb.Lq <= (path == PATH_FUSED ? 8192 : 2048);
+         pb.q1 == pb.Lq && pb.Lk <= 65536 && pb.k <= 512 &&
+         (pb.Lk > ROWS_MAX_LK ? 4 * ((pb.Lk + 15) / 16) >= 5 * pb.k && pb.BH * pb.Lq <= (path == PATH_FUSED ? 8192 : 2048)
+                              : !rows_ok(pb) && rows_few(pb) && pb.k <= ROWS_MAX_K && pb.BH * pb.Lq <= 8192);
 }
 
 void choose_long_path(const Problem& pb, Plan* pl) {
@@ -175,8 +177,8 @@ void choose_long_path(const Problem& pb, Plan* pl) {
     if (filter_ok(pb)) pl->path = PATH_FILTER;
     return;
   }
-  if (pb.Lk <= ROWS_MAX_LK) {  // runs as short rows (rows_ok); topk_attn_path reports it as path 1
-    pl->path = PATH_FUSED;
+  if (pb.Lk <= ROWS_MAX_LK) {  // short rows (rows_ok) are reported as path 1
+    pl->path = rows_ok(pb) ? PATH_FUSED : PATH_TILE;
     return;
   }
   // Threshold mode, see sample_rule: needs at least 2R sampled 16-key blocks in the

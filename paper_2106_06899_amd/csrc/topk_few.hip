@@ -117,6 +117,7 @@ __global__ __launch_bounds__(64) void k_few_select(Problem pb, Pass ps, PassBufs
   uint32_t lo = wave_extreme_u32_full<false>(mn), hi = top + 1;
   int clo = nb;
   const int enough = k + k / 8 + 4;
+  if (nb < k) lo = 0;  // fewer blocks than k (at most 1024 keys, which the candidates hold): every key
   for (int it = 0; clo > enough && hi - lo > 1; ++it) {
     uint32_t t = lo + (hi - lo) / 2;
     if (it < 24) {

@@ -100,8 +100,20 @@ struct ScanCfg {
 // size. The feature sizes are those the kernel is built for. Longer rows would not fit
 // a workgroup's LDS at 32 rows each; more than 256 kept keys would need more sort scratch.
 constexpr int ROWS_MAX_LK = 1024, ROWS_MAX_K = 256;
+// Except for a handful of bf16 queries per head against so many keys and values that they come
+// from memory: the kernel reads every value row, the general paths (few queries up to 8192
+// rows, chunk tiles beyond) only the selected ones. The line lies where keys and values
+// together pass 200 MB, about what the caches hold. Measured (us, this kernel / the general
+// paths; in brackets before this kernel): one query per head, k = 64: 768 heads of 1024 keys, d
+// 64 (201 MB) 46 / 47; 2048 heads 130 / 76 (100); 4096 heads, d 128 641 / 255 (304); of 256 keys,
+// d 64 48 / 54; 512 heads of 1024, d 128, k 128 84 / 46 (72). Eight queries, 4096 heads of 1024,
+// d 64 288 / 292 (457), d 128 674 / 429 (625). With more queries to share the reads this kernel
+// was never the slower one than before it: sixteen, 1024 heads of 1024, d 128 196 (244).
+inline bool rows_few(const Problem& pb) {
+  return pb.dtype == T_BF16 && !pb.causal && pb.Lq <= 8 && pb.Lk > 256 && pb.BH * pb.Lk * pb.d * 4 > 210000000;
+}
 inline bool rows_ok(const Problem& pb) {
-  return !pb.tile_only && pb.Lk <= ROWS_MAX_LK && pb.k <= ROWS_MAX_K &&
+  return !pb.tile_only && pb.Lk <= ROWS_MAX_LK && !rows_few(pb) && pb.k <= ROWS_MAX_K &&
          (pb.d == 32 || pb.d == 64 || pb.d == 96 || pb.d == 128);
 }
 hipError_t launch_rows(const Problem& pb, hipStream_t st);

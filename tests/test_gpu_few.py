@@ -123,3 +123,36 @@ def test_scan_ablation_of_few_queries(score_only):
     tk.profile_begin()
     tk.scan_ablation(q, k, 64, score_only=score_only)
     assert tk.profile_end()["score"][1] == 1
+
+
+# (heads, Lq, Lk, d, k): fewer, as many and more 16-key blocks than k; the smallest and largest
+# rows; more rows than the few-query kernels take (the last: chunk tiles)
+SHORT = [(410, 1, 1024, 128, 20), (830, 2, 1000, 64, 63), (412, 3, 1023, 128, 64), (820, 8, 1024, 64, 65), (1700, 1, 300, 128, 256),
+         (6400, 1, 257, 32, 17), (3280, 4, 257, 64, 200), (1100, 8, 520, 96, 100)]
+
+
+@pytest.mark.parametrize("case", SHORT)
+def test_few_queries_against_many_short_rows(case):
+    """Heads of at most 1024 keys whose keys and values together exceed the caches: a handful of
+    queries takes the general paths, more queries or fewer heads the short-row kernel (256 bytes
+    of workspace). Against 64 bits."""
+    H, Lq, Lk, d, k = case
+    print("[case]", case, flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    q, kk, v = (torch.randn(1, H, n, d, generator=gen, device="cuda").bfloat16() for n in (Lq, Lk, Lk))
+    assert tk.attn_path(1, H, Lq, Lk, d, k) == 2 and tk.attn_workspace_bytes(1, H, Lq, Lk, d, k) > 256
+    assert tk.attn_workspace_bytes(1, H, 9, Lk, d, k) == 256 and tk.attn_workspace_bytes(1, H // 2, Lq, Lk, d, k) == 256
+    out, idx, sc = tk.attn(q, kk, v, k, debug=True)
+    assert tk.last_fallback_rows() == 0
+    s = q.double() @ kk.double().transpose(2, 3).contiguous()
+    got = s.gather(3, idx.long())
+    # 32-bit sums of up to 128 products of size 1: scores this close may swap
+    assert bool(((got - s.topk(k, dim=-1).values).abs() <= 1e-4).all()) and bool(((sc.double() - got).abs() <= 1e-4).all())
+    assert k == 1 or bool((idx.long().sort(-1).values.diff(dim=-1) > 0).all())
+    w = torch.softmax(got * d ** -0.5, -1)
+    for h in range(0, H, 64):
+        p = torch.zeros_like(s[:, h:h + 64]).scatter_(3, idx[:, h:h + 64].long(), w[:, h:h + 64])
+        ref = p @ v[:, h:h + 64].double()
+        assert bool(((out[:, h:h + 64].double() - ref).abs() <= 2.0 ** -8 * ref.abs() + 1e-5).all())
+    for C in (1, 3):
+        assert torch.equal(tk.attn(q, kk, v, k, C), out)
