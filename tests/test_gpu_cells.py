@@ -24,6 +24,17 @@ def _lists(fn):
         tk.set_backward_lists(tk.TOPK_LISTS_AUTO)
 
 
+def _attn_by_cells(B, H, Lq, Lk, d, k):
+    """Whether such a backward pass runs by cells: its workspace is not the lists'."""
+    f = lambda: tk.lib().topk_attn_backward_workspace_bytes(B, H, Lq, Lk, d, k, tk.TOPK_BF16)
+    return f() != _lists(f)
+
+
+def _ffn_by_cells(N, dm, dff, k):
+    f = lambda: tk.lib().topk_ffn_backward_workspace_bytes(N, dm, dff, k, tk.TOPK_BF16)
+    return f() != _lists(f)
+
+
 def _close(a, b):
     """Two bf16 results of the same sums in different orders: neighbouring bf16 numbers at
     most, which lie up to 2^-7 of their size apart; held to each row's largest entry."""
@@ -33,14 +44,16 @@ def _close(a, b):
 
 
 # rows around the 64-row strips and 128-row tiles, units around the 64-key cells (4096 units
-# of few rows split the products); column tiles of 256 that d fills, half fills and repeats
+# of few rows split the products); column tiles of 256 that d fills, half fills and repeats; the
+# most units a strip's bitmap holds
 FFN_CASES = [(1, 256, 64, 2), (63, 768, 300, 40), (65, 288, 129, 129), (130, 1024, 513, 20), (300, 512, 4096, 128),
-             (257, 256, 2000, 512)]
+             (257, 256, 2000, 512), (100, 256, 16384, 410), (70, 256, 16377, 410)]
 
 
 @pytest.mark.parametrize("case", FFN_CASES)
 def test_ffn_cells(case):
     N, dm, dff, k = case
+    assert _ffn_by_cells(*case)
     w = wl.WORKLOADS["c5"].scaled(N=N, d_model=dm, d_ff=dff, k=k, chunk=64)
     print("[case]", w, flush=True)
     x = wl.make_inputs(w)
@@ -62,6 +75,7 @@ ATTN_CASES = [(8, 16, 70, 90, 128, 20, False), (8, 16, 70, 70, 128, 20, True), (
 @pytest.mark.parametrize("case", ATTN_CASES)
 def test_attention_cells(case):
     B, H, Lq, Lk, d, k, causal = case
+    assert _attn_by_cells(B, H, Lq, Lk, d, k)
     w = wl.WORKLOADS["c4"].scaled(B=B, H=H, Lq=Lq, Lk=Lk, d=d, k=k, causal=causal, scale=float(np.float32(d ** -0.5)))
     print("[case]", w, flush=True)
     x = wl.make_inputs(w)
@@ -80,6 +94,34 @@ def test_attention_cells(case):
         parity.check_grad_rows(n, p[-1:, hs], r, m, w.dtype)
     for p, r in zip(got, _lists(lambda: tk.attn_backward(q, kk, v, idx, dots, gd, w.scale))):
         _close(p, r)
+
+
+@pytest.mark.parametrize("causal", [False, True])
+def test_attention_cells_long_products(causal):
+    """12 heads of 4200: products of 66 cells in one part (the ranges are read 64 cells at a time), more
+    pairs a strip (17920) than the softmax's pass holds in registers. One head against the oracle
+    at sampled rows and keys."""
+    H, L, d, k = 12, 4200, 128, 280
+    assert _attn_by_cells(1, H, L, L, d, k)
+    w = wl.WORKLOADS["c4"].scaled(B=1, H=H, Lq=L, Lk=L, d=d, k=k, causal=causal, scale=float(np.float32(d ** -0.5)))
+    print("[case]", w, flush=True)
+    x = wl.make_inputs(w)
+    q, kk, v = (parity.to_dev(x[n]) for n in ("Q", "K", "V"))
+    _, idx, dots = tk.attn(q, kk, v, k, 0, causal, w.scale, cache=True)
+    g = parity.grad_out((1, H, L, d), w.dtype, 33)
+    gd = parity.to_dev(g)
+    got = tk.attn_backward(q, kk, v, idx, dots, gd, w.scale)
+    for p, r in zip(got, tk.attn_backward(q, kk, v, idx, dots, gd, w.scale)):
+        assert torch.equal(p, r)
+    for p, r in zip(got, _lists(lambda: tk.attn_backward(q, kk, v, idx, dots, gd, w.scale))):
+        _close(p, r)
+    rows = np.array([0, 1, 63, 64, 300, 4095, 4096, 4150, L - 1])
+    keys = np.array([0, 5, 63, 64, 1000, 4095, 4096, 4100])
+    hd = H - 1
+    ref, mag = bo.sampled_backward(*(x[n].values[0, hd] for n in ("Q", "K", "V")), idx[0, hd].cpu().numpy(), g.values[0, hd],
+                                   rows, keys, "softmax", w.scale, magnitudes=True)
+    for n, p, at, r, m in zip(("d_Q", "d_K", "d_V"), got, (rows, keys, keys), ref, mag):
+        parity.check_grad_rows(n, p[0, hd][torch.from_numpy(at).cuda()], r, m, w.dtype)
 
 
 def test_cells_keys_listed_twice_and_padding():

@@ -1,7 +1,8 @@
 """GPU test of the checked build (libtopk_check.so, compiled with TOPK_CHECK_INDICES):
 on each forward path it returns the same output bits as libtopk.so, its finalize sees
-no selected index outside the value matrix (topk_debug_bad_indices() == 0), and its
-calls, which wait for their stream, report no asynchronous kernel error."""
+no selected index outside the value matrix (topk_debug_bad_indices() == 0; the short-row
+kernel has no finalize and gathers by no index), and its calls, which wait for their stream,
+report no asynchronous kernel error."""
 import ctypes
 
 import pytest
@@ -36,11 +37,13 @@ def _stream():
 
 
 CASES = {
-    "fused_all_keys": ("c2", dict(B=1, H=2, Lq=300, Lk=512, chunk=128)),
+    "short_rows": ("c2", dict(B=1, H=2, Lq=300, Lk=512, chunk=128)),
+    "short_rows_fp32": ("c1", dict(Lq=300, Lk=500, chunk=100)),
+    "few_queries": ("c4", dict(B=1, H=2, Lq=20, Lk=9000, causal=False, chunk=20)),
     "fused_sampled": ("c3", dict(H=2, Lq=700, Lk=9000, chunk=256)),
-    "chunk_tile_causal": ("c4", dict(B=1, H=2, Lq=400, Lk=400, chunk=128)),
-    "filtered_causal": ("c4", dict(B=1, H=1, Lq=512, Lk=6000, causal=False, chunk=256)),
-    "fp32": ("c1", dict(Lq=300, Lk=500, chunk=100)),
+    "chunk_tile_causal": ("c4", dict(B=1, H=2, Lq=1400, Lk=1400, chunk=128)),
+    "filtered": ("c4", dict(B=1, H=1, Lq=512, Lk=6000, causal=False, chunk=256)),
+    "fp32": ("c1", dict(Lq=300, Lk=1500, chunk=100)),
 }
 
 
@@ -48,12 +51,14 @@ CASES = {
 def test_checked_build_attention(name):
     base, kw = CASES[name]
     w = wl.WORKLOADS[base].scaled(**kw)
+    dt = tk.TOPK_BF16 if w.dtype == wl.BF16 else tk.TOPK_F32
+    short = tk.attn_workspace_bytes(w.B, w.H, w.Lq, w.Lk, w.d, w.k, w.chunk, w.causal, dt) == 256
+    assert short == name.startswith("short_rows")
     x = wl.make_inputs(w)
     q, k, v = (parity.to_dev(x[n]) for n in ("Q", "K", "V"))
     ref = tk.attn(q, k, v, w.k, w.chunk, w.causal, w.scale)
     got = torch.empty_like(q)
     L = _checked()
-    dt = tk.TOPK_BF16 if w.dtype == wl.BF16 else tk.TOPK_F32
     rc = L.topk_attn(q.data_ptr(), k.data_ptr(), v.data_ptr(), got.data_ptr(), w.B, w.H, w.Lq, w.Lk, w.d, w.k,
                      w.chunk, int(w.causal), w.scale, dt, _stream())
     assert rc == 0, L.topk_last_error().decode()

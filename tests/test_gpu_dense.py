@@ -44,6 +44,11 @@ CASES = {
     "d128": dict(B=1, H=2, Lq=200, Lk=333, d=128, chunk=64, causal=False),
     "d128_causal": dict(B=1, H=1, Lq=260, Lk=260, d=128, chunk=1000, causal=True),
     "lq_above_lk_causal": dict(B=1, H=1, Lq=200, Lk=70, d=64, chunk=64, causal=True),
+    # around the 64-key tiles and the workgroups' query blocks, fewer and more keys than queries
+    "causal_tile_edges_wide": dict(B=1, H=2, Lq=129, Lk=257, d=64, chunk=65, causal=True),
+    "causal_tile_edges_tall": dict(B=1, H=1, Lq=385, Lk=191, d=128, chunk=385, causal=True),
+    "tile_edges": dict(B=1, H=2, Lq=127, Lk=64, d=128, chunk=127, causal=False),
+    "tile_edges_long": dict(B=1, H=1, Lq=257, Lk=1025, d=64, chunk=256, causal=False),
     "single_key": dict(B=1, H=1, Lq=5, Lk=1, d=64, chunk=2, causal=False),
 }
 
@@ -101,3 +106,24 @@ def test_dense_tiny_weights(d, at):
     want = np.exp(-90.0) * 2.0 ** 120
     # 2^-130 as a bf16 number: a multiple of 2^-133
     assert bool(((out - want).abs() <= (2.0 ** -4 + 2.0 ** -8) * want).all()), out.flatten()[0]
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("causal", [False, True])
+def test_dense_infinities(d, causal):
+    """Scores of -inf (weight 0) in parts of tiles and whole tiles, before and after finite ones."""
+    gen = torch.Generator(device="cuda").manual_seed(6)
+    L = 330
+    q, k, v = (torch.randn(1, 1, L, d, generator=gen, device="cuda") for _ in range(3))
+    q[..., 0], k[..., 0] = 1.0, 0.0
+    away = torch.zeros(L, dtype=torch.bool, device="cuda")
+    away[1:130], away[200:300] = True, True
+    k[0, 0, away, 0] = -float("inf")
+    q, k, v = q.bfloat16(), k.bfloat16(), v.bfloat16()
+    out = tk.attn_dense(q, k, v, 0, causal, 0.125)[0, 0].double()
+    s = 0.125 * (q[0, 0].double() @ k[0, 0].double().masked_fill(away[:, None], 0).t())
+    s = s.masked_fill(away[None, :], -float("inf"))
+    if causal:
+        s = s.masked_fill(~torch.ones(L, L, dtype=torch.bool, device="cuda").tril(), -float("inf"))
+    ref = torch.softmax(s, -1) @ v[0, 0].double()
+    assert bool(((out - ref).abs().amax(-1) <= parity.RTOL[wl.BF16] * ref.abs().amax(-1)).all())

@@ -45,26 +45,32 @@ def test_mfma_lane_layout():
 
 
 ATTN_CASES = {
-    # name: (base workload, overrides)
-    "c1_fp32_tile": ("c1", dict(Lq=300, Lk=777, chunk=100)),
-    "c2_bf16_fused_all": ("c2", dict(B=2, H=3, Lq=200, Lk=512, chunk=128)),
-    "c2_bf16_fused_all_ragged": ("c2", dict(B=1, H=2, Lq=130, Lk=333, chunk=64)),
-    # every key a candidate and more than 512 of them: the select's long-list path
-    "c2_bf16_fused_all_long_lists": ("c2", dict(B=1, H=2, Lq=150, Lk=1000, chunk=64)),
+    # name: (base workload, overrides). Names in rows_ run the short-row kernel, those in few_ the
+    # few-query kernels, those in tile_ the chunk tiles, those in filter_ the filtered path
+    # (test_attn_cases_take_the_path_they_name)
+    "tile_c1_fp32": ("c1", dict(Lq=300, Lk=1777, chunk=100)),
+    "rows_c1_fp32": ("c1", dict(Lq=300, Lk=777, chunk=100)),
+    "rows_c2_bf16": ("c2", dict(B=2, H=3, Lq=200, Lk=512, chunk=128)),
+    "rows_c2_bf16_ragged": ("c2", dict(B=1, H=2, Lq=130, Lk=333, chunk=64)),
+    "rows_c2_bf16_long": ("c2", dict(B=1, H=2, Lq=150, Lk=1000, chunk=64)),
     "c3_bf16_fused_sample": ("c3", dict(H=2, Lq=300, Lk=9000, chunk=256)),
     "c3_bf16_fused_sample_k32": ("c3", dict(H=1, Lq=257, Lk=4600, k=32, chunk=1024)),
-    "c4_bf16_causal_tile": ("c4", dict(B=1, H=2, Lq=600, Lk=600, chunk=256)),
+    "tile_c4_bf16_causal": ("c4", dict(B=1, H=2, Lq=1100, Lk=1100, chunk=256)),
+    "rows_c4_bf16_causal": ("c4", dict(B=1, H=2, Lq=600, Lk=600, chunk=256)),
     "c4_d128_fused_sample": ("c4", dict(B=1, H=1, Lq=200, Lk=17000, causal=False, chunk=128)),
-    "c4_d128_fused_all": ("c4", dict(B=1, H=2, Lq=150, Lk=700, causal=False, chunk=64)),
-    "bf16_tile_d96": ("c2", dict(B=1, H=2, Lq=70, Lk=300, d=96, k=40, chunk=32)),
-    "fp32_causal_tile": ("c1", dict(Lq=200, Lk=260, causal=True, k=20, chunk=64)),
+    "rows_c4_d128": ("c4", dict(B=1, H=2, Lq=150, Lk=700, causal=False, chunk=64)),
+    "tile_bf16_d96": ("c2", dict(B=1, H=2, Lq=140, Lk=1300, d=96, k=40, chunk=32)),
+    "rows_bf16_d96": ("c2", dict(B=1, H=2, Lq=70, Lk=300, d=96, k=40, chunk=32)),
+    "tile_fp32_causal": ("c1", dict(Lq=1200, Lk=1260, causal=True, k=20, chunk=64)),
+    "rows_fp32_causal": ("c1", dict(Lq=200, Lk=260, causal=True, k=20, chunk=64)),
     # chunk-tile short-row select past 1024 keys: exact sampled rank (R > 96) and
     # the per-lane top-two threshold (R <= 96)
     "tile_sampled_exact_rank": ("c2", dict(B=1, H=1, Lq=90, Lk=1500, d=96, k=128, chunk=64)),
     "tile_sampled_top_two": ("c2", dict(B=1, H=1, Lq=90, Lk=6000, d=96, k=64, chunk=64, dtype=wl.F32)),
     # chunk-tile long-row select (workgroup per row, sampled blocks) and a causal
     # case whose rows cross 1024 keys
-    "tile_long_rows": ("c2", dict(B=1, H=1, Lq=40, Lk=9500, d=96, k=300, chunk=40)),
+    "tile_long_rows": ("c2", dict(B=1, H=1, Lq=40, Lk=9500, d=96, k=300, chunk=40, dtype=wl.F32)),
+    "few_long_rows": ("c2", dict(B=1, H=1, Lq=40, Lk=9500, d=96, k=300, chunk=40)),
     "c4_causal_long": ("c4", dict(B=1, H=1, Lq=2100, Lk=2100, chunk=1024)),
     # causal masks with Lk >= 256 k: rows below 1024 R on the chunk-tile path, the
     # rest on the fused path (path 3)
@@ -82,9 +88,29 @@ ATTN_CASES = {
     "filter_causal_d128_k300": ("c4", dict(B=1, H=1, Lq=5000, Lk=5000, k=300, chunk=1000)),
     # a handful of rows of 563 samples each: the threshold kernel's loads (1024 samples
     # from each row's start) run past the last row into the padding after the samples
-    "filter_d96_few_rows": ("c2", dict(B=1, H=1, Lq=3, Lk=9000, d=96, k=200, chunk=3)),
-    "filter_d128_few_rows": ("c4", dict(B=1, H=1, Lq=2, Lk=9000, k=200, causal=False, chunk=2)),
+    # (k above 4/5 of the 563 blocks of 16 keys: not for the few-query kernels)
+    "filter_d96_few_rows": ("c2", dict(B=1, H=1, Lq=3, Lk=9000, d=96, k=460, chunk=3)),
+    "filter_d128_few_rows": ("c4", dict(B=1, H=1, Lq=2, Lk=9000, k=460, causal=False, chunk=2)),
+    "few_d96": ("c2", dict(B=1, H=1, Lq=3, Lk=9000, d=96, k=200, chunk=3)),
+    "few_d128": ("c4", dict(B=1, H=1, Lq=2, Lk=9000, k=200, causal=False, chunk=2)),
 }
+
+
+def test_attn_cases_take_the_path_they_name():
+    """Told apart by the workspace where the reported path is the same: 256 bytes for the short-row
+    kernel, a block maximum beside every 16 scores for few queries, none for chunk tiles."""
+    for name, (base, kw) in ATTN_CASES.items():
+        w = wl.WORKLOADS[base].scaled(**kw)
+        dt = tk.TOPK_BF16 if w.dtype == wl.BF16 else tk.TOPK_F32
+        path = tk.attn_path(w.B, w.H, w.Lq, w.Lk, w.d, w.k, w.chunk, w.causal, dt)
+        ws = tk.attn_workspace_bytes(w.B, w.H, w.Lq, w.Lk, w.d, w.k, w.chunk, w.causal, dt)
+        kind = name.split("_")[0]
+        assert (kind == "rows") == (ws == 256), name
+        if kind in ("tile", "few"):
+            rows = w.B * w.H * -(-w.Lq // w.chunk) * w.chunk
+            assert path == 2 and (kind == "few") == (ws >= rows * ((w.Lk + 15) // 16 * 68 + 8 * w.k)), name
+        if kind == "filter":
+            assert path == 4, name
 
 
 @pytest.mark.parametrize("name", sorted(ATTN_CASES))
@@ -147,9 +173,10 @@ def test_sliced_gather_plain_equals_debug(name):
 
 
 @pytest.mark.parametrize("base,kw", [
-    ("c2", dict(B=1, H=2, Lq=100, Lk=512)),                 # fused, all candidates
+    ("c2", dict(B=1, H=2, Lq=100, Lk=512)),                 # short rows
     ("c3", dict(H=1, Lq=150, Lk=9000)),                     # fused, sampled threshold
-    ("c4", dict(B=1, H=1, Lq=100, Lk=300)),                 # chunk-tile, causal
+    ("c4", dict(B=1, H=1, Lq=100, Lk=300)),                 # short rows, causal
+    ("c4", dict(B=1, H=1, Lq=1100, Lk=1100)),               # chunk-tile, causal
 ])
 def test_k1_returns_argmax_value_row_exactly(base, kw):
     """k = 1: the single survivor has softmax weight exactly 1, so the bf16 output is
@@ -196,6 +223,8 @@ def test_k_equals_Lk_is_vanilla_attention(base, kw):
     ("c3", dict(H=1, Lq=300, Lk=9000)),
     ("c4", dict(B=1, H=1, Lq=300, Lk=300)),
     ("c1", dict(Lq=200, Lk=300)),
+    ("c1", dict(Lq=200, Lk=1300)),                          # chunk-tile, fp32
+    ("c4", dict(B=1, H=1, Lq=1200, Lk=1200)),               # chunk-tile, causal
     ("c3", dict(H=1, Lq=4200, Lk=4200, k=16, causal=True)),
     ("c4", dict(B=1, H=1, Lq=2500, Lk=2500)),
 ])
@@ -422,10 +451,12 @@ def test_one_chunk_per_pass_is_bit_identical(base, kw, path):
 # and differ only low in the score or in the index.
 TIE_CASES = [
     ("c3", dict(H=2, Lq=300, Lk=6000, chunk=256), 1),        # fused path, sampled threshold
-    ("c2", dict(B=1, H=2, Lq=200, Lk=512, chunk=128), 1),     # fused path, every key a candidate
+    ("c2", dict(B=1, H=2, Lq=200, Lk=512, chunk=128), 1),     # short rows
     ("c4", dict(B=1, H=2, Lq=300, Lk=4096, chunk=128), 4),    # filtered chunk-tile path (causal)
     ("c5", dict(N=200, d_model=256, d_ff=3000, k=256, chunk=64), 4),  # filtered chunk-tile (FFN)
-    ("c1", dict(Lq=200, Lk=700, chunk=64), 2),                # chunk-tile path, fp32
+    ("c1", dict(Lq=200, Lk=700, chunk=64), 2),                # short rows, fp32
+    ("c1", dict(Lq=200, Lk=1700, chunk=64), 2),               # chunk-tile path, fp32
+    ("c4", dict(B=1, H=1, Lq=1100, Lk=1100, chunk=128), 2),   # chunk-tile path, bf16 (causal)
 ]
 
 

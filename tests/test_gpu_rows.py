@@ -20,6 +20,8 @@ CASES = [
     (1, 2, 530, 511, 64, 20, True), (1, 1, 31, 513, 96, 256, False), (1, 1, 20, 1000, 128, 200, False),
     (1, 1, 1100, 1024, 64, 100, True), (16, 32, 33, 130, 64, 40, False), (32, 16, 31, 520, 128, 128, False),
     (16, 32, 20, 300, 96, 3, True), (16, 32, 5, 1024, 32, 200, False),
+    # the 32-row kernels of d = 128 that keep some registers in scratch memory
+    (16, 32, 33, 250, 128, 60, False), (16, 32, 20, 500, 128, 100, True),
 ]
 
 
@@ -29,6 +31,7 @@ def test_short_rows(case, dtype):
     B, H, Lq, Lk, d, k, causal = case
     w = wl.WORKLOADS["c2"].scaled(B=B, H=H, Lq=Lq, Lk=Lk, d=d, k=k, causal=causal, dtype=dtype, chunk=7)
     print("[case]", w, flush=True)
+    assert tk.attn_workspace_bytes(B, H, Lq, Lk, d, k, 7, causal, tk.TOPK_BF16 if dtype == wl.BF16 else tk.TOPK_F32) == 256
     x = wl.make_inputs(w)
     out, idx, sc = parity.run_attn(w, x)
     rows = parity.sample_attn_rows(w, min(400, B * H * Lq), seed=5)
