@@ -24,9 +24,10 @@
 // its row alone, from its own pairs.
 //
 // Bound by latency (two waves a SIMD: 70 KB of LDS a workgroup) and, for wide rows, by the
-// matrix instructions and the taking apart, about 45 vector instructions per 12 of them. Whole backward pass, lists -> cells: 16384 tokens, d_model 768, 512
-// of 4096 units: 5290 -> 1040 us; of 16384: 6230 -> 2760; 48 heads of 1024 tokens, d = 64,
-// k = 64: 264 -> 195; 16 heads of 2048, d = 128, k = 128: 390 -> 256.
+// matrix instructions and the taking apart, about 45 vector instructions per 12 of them. Whole
+// backward pass, lists -> cells: 16384 tokens, d_model 768, 512 of 4096 units: 5260 -> 1445 us;
+// of 16384: 6220 -> 4120; 48 heads of 1024 tokens, d = 64, k = 64: 247 -> 215; 32 heads of 2048,
+// d = 128, k = 128: 717 -> 556 (causal 719 -> 582).
 #include "topk_device.h"
 #include "topk_internal.h"
 

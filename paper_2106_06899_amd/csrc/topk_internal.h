@@ -232,23 +232,55 @@ hipError_t launch_cells_products(const BwdProblem& bp, const CellBufs& cb, hipSt
 hipError_t launch_backward_cells(const BwdProblem& bp, const CellBufs& cb, hipStream_t st);
 
 // Where the products by cells take the place of the gathers by lists (bf16, automatic
-// lists). The gathers' time goes with the pairs and the row size, the products' with rows
-// x keys; each cell also costs them a fixed 2000 to 5000 cycles, which wide rows hide.
-// Measured (us, lists / cells): d >= 256: keys per kept key 8: 5290 / 1040, 16: 5570 /
-// 1650, 32: 6230 / 2760 and (d 256) 410 / 306, 43: 4710 / 2650, 64: 690 / 675. d = 128: 16:
-// 390 / 256 (causal 370 / 325), 32: 760 / 705 and (8192 causal) 1540 / 1780; a head of 700
-// rows 50 / 63: too few workgroups. d = 64 pays only on short rows, whose lists are dearer:
-// 48 heads of 1024, 16: 264 / 195; 12 heads of 2048, 16: 196 / 210.
+// lists): where no shape that was measured is slower by more than the runs differ. The gathers'
+// time goes with the pairs and the row size (0.8 ps per pair and feature), and with few rows
+// with k (about 0.8 us a kept key); the products' with rows x keys (6 ps at d = 256, 15 to 18 at
+// 768 to 1024) and, in few workgroups, with the longest walk along a head's cells.
+// The causal mask, which the backward pass is not told of, leaves the gathers their time and
+// makes those walks uneven. Measured (us, lists / cells; c: causal):
+//  d = 64: 32 heads of 1024, k 64 176 / 148, c 175 / 184; 40 of 1000, 63 209 / 213; 48 of 1024, 64
+//   247 / 215, c 248 / 238; 43 of 768, 48 168 / 169, c 173 / 141; 64 of 512, 32 171 / 94, c 173 / 107;
+//   longer heads 24 of 1500, 94 217 / 293; 12 of 2048, 128 189 / 238.
+//  d = 128, one key in 16: 32 heads of 512 117 / 88, c 120 / 96; of 1024: 16 138 / 120, c 139 / 153; 24
+//   187 / 162, c 191 / 201; 32 236 / 169, c 236 / 212; of 2048: 16 359 / 301, c 355 / 378; 24 535 / 474, c
+//   534 / 474; one in 12: 16 of 2048 471 / 333, c 465 / 431; one in 32: 16 of 4096 726 / 902; k 512: 2 of
+//   8192 779 / 667, c 1063 / 910. d = 160: 16 of 1024, 64 205 / 150, c 207 / 178.
+//  d = 256: 16 heads of 1024, k 64 203 / 160, c 208 / 188; 8 of them 129 / 125, c 135 / 145; one key in
+//   24: 8 of 2048 249 / 246, c 247 / 283; k 256: 1 head of 4096 221 / 200, c 340 / 295.
+//  Feed-forward d = 256: 4096 tokens and units: k 256 221 / 189, 170 161 / 170; 512 tokens, 1024, 64 60
+//   / 73; 8192, 1024, 64 187 / 146; 8192, 4096, 170 280 / 274; 8192, 8192, 256 422 / 478; 8192, 16384, 512
+//   922 / 802.
+//  d >= 512 (tokens, d, units, k): 512, 512, 1024, 64 89 / 82; 512, 768, 768, 32 72 / 83; 2048, 768, 300, 20
+//   130 / 97; 2048, 512, 4096, 170 210 / 170; 4096, 1024, 2048, 85 247 / 260; 4096, 512, 4096, 128 218 / 257;
+//   16384 of these 800 / 768; 128 of these 131 / 87; 4096, 768, 4096, 128 355 / 339, k 100 295 / 335; 2048, 1024,
+//   8192, 256 468 / 394; 2048, 768, 16384, 410 688 / 580; 8192, 768, 8192, 200 1103 / 1177; 16384 of these
+//   2365 / 2270; 16384, 768, 4096, 512 5263 / 1445; 64, 1024, 2048, 64 86 / 76; 1, 768, 4096, 512 402 / 79.
 inline bool cells_ok(const BwdProblem& bp) {
   if (bp.list_mode != 0 || bp.dtype != T_BF16 || bp.d % 32 != 0 || bp.Lk > (int64_t)64 * CELL_MAX) return false;
   // every launch below 2^32 threads: 1024 a strip; 256 a tile of the products, whose column
   // tiles (at most four) and two sides make eight at most
   const int64_t tq = (bp.Lq + 127) / 128, tk = (bp.Lk + 127) / 128;
   if (bp.BH * ((bp.Lq + 63) / 64) >= 1 << 22 || bp.BH * (tq > tk ? tq : tk) * 8 >= 1 << 24 || bp.BH * tq * tk >= 1 << 24) return false;
-  if (bp.d >= 256) return bp.Lk <= 40 * bp.k;
-  const int64_t tiles = bp.BH * ((bp.Lq + 127) / 128);
-  if (bp.d >= 128) return bp.Lk <= 16 * bp.k && tiles >= 128;
-  return bp.d == 64 && bp.Lk <= 1024 && bp.Lk <= 16 * bp.k && tiles >= 256;
+  const int64_t d = bp.d, k = bp.k, Lk = bp.Lk, tiles = bp.BH * tq;
+  if (d == 64) return Lk <= 16 * k && Lk <= 1024 && tiles >= (Lk <= 768 ? 256 : 384);
+  if (d < 128) return false;
+  if (bp.act == ACT_SOFTMAX || d < 256) {
+    if (Lk > 16 * k) return false;
+    if (k >= (d >= 256 ? 256 : 512) && tiles >= (d >= 256 ? 16 : 64)) return true;
+    return tiles >= (d > 128 || Lk <= 512 ? 128 : Lk <= 1024 || Lk <= 12 * k ? 256 : 384);
+  }
+  const int64_t N = bp.Lq;
+  int64_t most = 0;  // units per kept unit
+  if (d >= 512) {
+    if (k >= 64 || N >= 2048) most = 16;
+    if (k >= 128 || N >= 8192) most = 25;
+    if (k >= 256 || (k >= 128 && d >= 768) || (k >= 64 && N <= 128) || N >= 16384) most = 32;
+    if (k >= 400 || (k >= 200 && N >= 16384)) most = 40;
+  } else {
+    if (k >= 128 || N >= 8192) most = N >= 8192 ? 25 : 16;
+    if (k >= 512 && N >= 8192) most = 32;
+  }
+  return Lk <= most * k;
 }
 hipError_t launch_filter(const Problem& pb, const Pass& ps, const PassBufs& b, int stage, hipStream_t st);
 hipError_t launch_filter_scan(const Problem& pb, const Pass& ps, const PassBufs& b, hipStream_t st);

@@ -70,7 +70,7 @@ def test_set_workspace_validation():
 
 
 def test_path_choice_for_the_five_workloads():
-    # c1 fp32 -> chunk-tile; c2 short rows -> fused (every key a candidate);
+    # c1 and c2: short rows, one kernel, reported as the path longer rows of their kind take;
     # c3 long rows -> fused (sampled threshold); c4 causal -> filtered chunk-tile; c5 FFN k 512 -> chunk-tile
     assert tk.attn_path(1, 1, 1024, 1024, 64, 32, 256, False, tk.TOPK_F32) == 2
     assert tk.attn_path(8, 12, 512, 512, 64, 64, 512, False, tk.TOPK_BF16) == 1
@@ -89,7 +89,7 @@ def test_workspace_is_linear_in_length_and_capped():
     assert all(s > 0 for s in sizes)
     assert sizes[1] <= 2.2 * sizes[0]
     assert max(sizes) <= (8 << 30) + (64 << 20)
-    tile = [tk.attn_workspace_bytes(1, 1, L, L, 64, 32, 256, False, tk.TOPK_F32) for L in (1024, 2048, 4096)]
+    tile = [tk.attn_workspace_bytes(1, 1, L, L, 64, 32, 256, False, tk.TOPK_F32) for L in (2048, 4096, 8192)]
     # chunk-tile path: one chunk costs O(C * Lk); the whole call O(L^2) until capped
     assert tile[1] > tile[0]
     assert tk.attn_workspace_bytes(1, 1, 10, 10, 64, 0) == 0
@@ -158,3 +158,31 @@ def test_causal_split_path():
     assert tk.attn_path(4, 16, 8192, 8192, 128, 128, 1024, True, tk.TOPK_BF16) == 4  # Lk < 256 k: filtered tiles
     assert tk.attn_path(1, 1, 4500, 4500, 64, 16, 512, True, tk.TOPK_F32) == 2
     assert tk.attn_workspace_bytes(1, 12, 65536, 65536, 64, 128, 1024, True) > 0
+
+
+def test_backward_takes_the_cells_where_they_were_faster():
+    """Told by the workspace, which is not the lists' one. Both sides of the rules' edges: rows too
+    narrow, too sparse, too few for the cells' latency, heads whose causal walks are too uneven."""
+    L = tk.lib()
+
+    def cells(f, *a):
+        n = f(*a, tk.TOPK_BF16)
+        tk.set_backward_lists(tk.TOPK_LISTS_BUCKET)
+        try:
+            return n != f(*a, tk.TOPK_BF16)
+        finally:
+            tk.set_backward_lists(tk.TOPK_LISTS_AUTO)
+
+    attn, ffn = L.topk_attn_backward_workspace_bytes, L.topk_ffn_backward_workspace_bytes
+    for B, H, n, d, k in [(4, 12, 1024, 64, 64), (1, 64, 512, 64, 32), (1, 32, 1024, 128, 64), (1, 24, 2048, 128, 128), (1, 16, 2048, 128, 171),
+                          (1, 2, 8192, 128, 512), (1, 16, 1024, 160, 64), (1, 16, 1024, 256, 64), (1, 1, 4096, 256, 256)]:
+        assert cells(attn, B, H, n, n, d, k), (H, n, d, k)
+    for B, H, n, d, k in [(1, 32, 1024, 64, 64), (1, 40, 1000, 64, 63), (1, 48, 1100, 64, 128), (1, 16, 2048, 128, 128), (1, 16, 1024, 128, 64),
+                          (1, 16, 4096, 128, 128), (1, 8, 2048, 128, 256), (1, 16, 1024, 96, 64), (1, 8, 1024, 256, 64), (1, 8, 2048, 256, 86)]:
+        assert not cells(attn, B, H, n, n, d, k), (H, n, d, k)
+    for N, d, u, k in [(16384, 768, 4096, 512), (16384, 768, 16384, 512), (4096, 256, 4096, 256), (8192, 256, 16384, 512), (512, 512, 1024, 64),
+                       (2048, 768, 300, 20), (4096, 768, 4096, 128), (1, 768, 4096, 512), (2048, 768, 16384, 410)]:
+        assert cells(ffn, N, d, u, k), (N, d, u, k)
+    for N, d, u, k in [(4096, 256, 4096, 128), (512, 256, 1024, 64), (8192, 256, 8192, 256), (512, 768, 768, 32), (2048, 1024, 2048, 64),
+                       (4096, 512, 4096, 128), (4096, 768, 4096, 100), (8192, 768, 8192, 200), (16384, 768, 65536, 512)]:
+        assert not cells(ffn, N, d, u, k), (N, d, u, k)

@@ -46,8 +46,8 @@ def _close(a, b):
 # rows around the 64-row strips and 128-row tiles, units around the 64-key cells (4096 units
 # of few rows split the products); column tiles of 256 that d fills, half fills and repeats; the
 # most units a strip's bitmap holds
-FFN_CASES = [(1, 256, 64, 2), (63, 768, 300, 40), (65, 288, 129, 129), (130, 1024, 513, 20), (300, 512, 4096, 128),
-             (257, 256, 2000, 512), (100, 256, 16384, 410), (70, 256, 16377, 410)]
+FFN_CASES = [(1, 512, 64, 64), (63, 768, 300, 64), (65, 288, 129, 129), (130, 1024, 513, 70), (300, 512, 4096, 171),
+             (257, 256, 2000, 512), (100, 512, 16384, 410), (70, 512, 16377, 410)]
 
 
 @pytest.mark.parametrize("case", FFN_CASES)
@@ -130,9 +130,10 @@ def test_cells_keys_listed_twice_and_padding():
     gen = torch.Generator(device="cuda").manual_seed(4)
     x, g = (torch.randn(200, 256, generator=gen, device="cuda").bfloat16() for _ in range(2))
     w1, w2 = (torch.randn(500, 256, generator=gen, device="cuda").bfloat16() for _ in range(2))
-    idx = torch.randint(-3, 520, (200, 40), generator=gen, device="cuda", dtype=torch.int32)
-    idx[:64] = torch.stack([torch.randperm(500, generator=gen, device="cuda")[:40] for _ in range(64)]).int()  # a strip without repeats
-    dots = torch.randn(200, 40, generator=gen, device="cuda")
+    assert _ffn_by_cells(200, 256, 500, 128)
+    idx = torch.randint(-3, 520, (200, 128), generator=gen, device="cuda", dtype=torch.int32)
+    idx[:64] = torch.stack([torch.randperm(500, generator=gen, device="cuda")[:128] for _ in range(64)]).int()  # a strip without repeats
+    dots = torch.randn(200, 128, generator=gen, device="cuda")
     got = tk.ffn_backward(x, w1, w2, idx, dots, g)
     for p, r in zip(got, _lists(lambda: tk.ffn_backward(x, w1, w2, idx, dots, g))):
         _close(p, r)
@@ -145,7 +146,9 @@ def test_cells_rows_not_finite(N, dff):
     gen = torch.Generator(device="cuda").manual_seed(5)
     x, g = (torch.randn(N, 256, generator=gen, device="cuda").bfloat16() for _ in range(2))
     w1, w2 = (torch.randn(dff, 256, generator=gen, device="cuda").bfloat16() for _ in range(2))
-    _, idx, dots = tk.ffn(x, w1, w2, 100, cache=True)
+    k = 128 if dff == 1000 else 256
+    assert _ffn_by_cells(N, 256, dff, k)
+    _, idx, dots = tk.ffn(x, w1, w2, k, cache=True)
     ref = _lists(lambda: tk.ffn_backward(x, w1, w2, idx, dots, g))
     bad = g.clone()
     bad[70] = float("inf")
@@ -187,7 +190,8 @@ def test_cells_need_more_workspace_than_lists():
 def test_cells_keep_32_bits(dm):
     """Weights and score gradients of 18 significant bits that cancel to their last bits: exact in 32
     bits (products of 18-bit integers and powers of two, sums that stay below 2^24), lost in 16."""
-    N, dff, k = 300, 700, 30
+    N, dff, k = 300, 700, 128
+    assert _ffn_by_cells(N, dm, dff, k)
     gen = torch.Generator(device="cuda").manual_seed(7)
     pow2 = lambda *s: (torch.randint(0, 2, s, generator=gen, device="cuda") * 2 - 1) * 2.0 ** torch.randint(-1, 2, s, generator=gen, device="cuda")
     big, near = 2.0 ** 17 + 257, 2.0 ** 17 + 255
@@ -198,10 +202,10 @@ def test_cells_keep_32_bits(dm):
     # units 0 .. 29, kept by tokens 0 and 100: their score gradients are `big` and `-near`
     x[100] = x[0]
     w2[:30], g[0], g[100] = row(512, 256, 1), row(256, 1, 1), row(-256, 0, -255)
-    idx[[0, 100]] = torch.arange(30, dtype=torch.int32, device="cuda")
+    idx[[0, 100], :30] = torch.arange(30, dtype=torch.int32, device="cuda")
     # units 600 .. 629, kept by tokens 5 and 290 with weights `big` and `near`
     g[290] = -g[5]
-    idx[[5, 290]] = torch.arange(600, 630, dtype=torch.int32, device="cuda")
+    idx[[5, 290], :30] = torch.arange(600, 630, dtype=torch.int32, device="cuda")
     dots[5], dots[290] = big, near
     # token 70 keeps units 300 and 500: score gradients `big` and `-near`
     w1[500] = w1[300]
@@ -226,8 +230,9 @@ def test_cells_closed_gate_at_a_key_that_is_not_finite(bad):
     gen = torch.Generator(device="cuda").manual_seed(8)
     x, g = (torch.randn(200, 256, generator=gen, device="cuda").bfloat16() for _ in range(2))
     w1, w2 = (torch.randn(500, 256, generator=gen, device="cuda").bfloat16() for _ in range(2))
-    idx = torch.stack([torch.randperm(499, generator=gen, device="cuda")[:40] + 1 for _ in range(200)]).int()
-    dots = torch.randn(200, 40, generator=gen, device="cuda")
+    assert _ffn_by_cells(200, 256, 500, 128)
+    idx = torch.stack([torch.randperm(499, generator=gen, device="cuda")[:128] + 1 for _ in range(200)]).int()
+    dots = torch.randn(200, 128, generator=gen, device="cuda")
     dots[idx == 7] = -1.0
     w1[7] = bad
     got = tk.ffn_backward(x, w1, w2, idx, dots, g)
@@ -254,7 +259,9 @@ def test_cells_rows_not_finite_repeat(N, dff):
     gen = torch.Generator(device="cuda").manual_seed(9)
     x, g = (torch.randn(N, 256, generator=gen, device="cuda").bfloat16() for _ in range(2))
     w1, w2 = (torch.randn(dff, 256, generator=gen, device="cuda").bfloat16() for _ in range(2))
-    _, idx, dots = tk.ffn(x, w1, w2, 100, cache=True)
+    k = 128 if dff == 1000 else 256
+    assert _ffn_by_cells(N, 256, dff, k)
+    _, idx, dots = tk.ffn(x, w1, w2, k, cache=True)
     w1[:, 3], x[:, 5] = float("inf"), float("inf")
     got = tk.ffn_backward(x, w1, w2, idx, dots, g)
     for _ in range(5):
@@ -275,9 +282,11 @@ def test_cells_keys_listed_often_repeat(N, dff):
     gen = torch.Generator(device="cuda").manual_seed(10)
     x, g = (torch.randn(N, 256, generator=gen, device="cuda").bfloat16() for _ in range(2))
     w1, w2 = (torch.randn(dff, 256, generator=gen, device="cuda").bfloat16() for _ in range(2))
-    idx = torch.randint(-1, 30, (N, 100), generator=gen, device="cuda", dtype=torch.int32)
-    idx[:, 50:] += dff - 30
-    dots = torch.randn(N, 100, generator=gen, device="cuda")
+    k = 128 if dff == 500 else 256
+    assert _ffn_by_cells(N, 256, dff, k)
+    idx = torch.randint(-1, 30, (N, k), generator=gen, device="cuda", dtype=torch.int32)
+    idx[:, k // 2:] += dff - 30
+    dots = torch.randn(N, k, generator=gen, device="cuda")
     got = tk.ffn_backward(x, w1, w2, idx, dots, g)
     for _ in range(5):
         for p, q in zip(got, tk.ffn_backward(x, w1, w2, idx, dots, g)):
