@@ -15,6 +15,8 @@ CASES = [
     (1, 1, 1025, 16, 5, 1, False), (2, 33, 1087, 48, 33, 32, False), (1, 129, 1089, 96, 100, 129, False),
     (2, 1100, 1100, 64, 40, 127, True), (1, 70, 1028, 272, 12, 64, False), (3, 31, 63, 16, 7, 5, False),
     (1, 300, 130, 256, 20, 128, True), (1, 40, 1200, 8, 9, 40, False),
+    # causal heads share the chip eight at a time, the rest tile by tile
+    (9, 230, 1100, 32, 12, 64, True), (3, 1300, 1300, 16, 30, 500, True), (16, 150, 1030, 16, 8, 150, True),
 ]
 
 
