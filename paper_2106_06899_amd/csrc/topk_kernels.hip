@@ -2176,8 +2176,10 @@ hipError_t launch_finalize(const Problem& pb, const Pass& ps, const PassBufs& b,
   // XCD's L2 caches its slice of the matrix only
   const int64_t esz = pb.dtype == T_BF16 ? 2 : 4, row = pb.d * esz;
   const int64_t rows = pb.BH * (pb.q1 - pb.q0);  // of the whole call, whatever the passes
-  if (rows <= 128 || (rows <= 512 && pb.k >= 128)) {  // see k_finalize_few
-    const int slices = (int)((row + 127) / 128);
+  const int slices = (int)((row + 127) / 128);
+  // see k_finalize_few; beyond 2048 workgroups there is nothing left to spread, and a row's slices read
+  // apart: 4 x 128 rows of 128, d = 1024: a call of 134 us took 156, d = 512 119 / 126
+  if (rows <= 128 || (rows <= 512 && pb.k >= 128 && rows * slices <= 2048)) {
     const unsigned gf = (unsigned)(pass_rows(pb, ps) * slices);
     if (pb.dtype == T_BF16) k_finalize_few<uint16_t><<<gf, 512, sh, st>>>(pb, ps, b.sel, b.sel_sorted, slices);
     else k_finalize_few<float><<<gf, 512, sh, st>>>(pb, ps, b.sel, b.sel_sorted, slices);
