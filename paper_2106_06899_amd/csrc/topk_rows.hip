@@ -517,9 +517,11 @@ hipError_t launch_rows_d(RowsArgs a, int64_t BH, hipStream_t st) {
   // registers spill, bf16 values at d = 96 and 128: 96 heads of 512, d = 128, 104 us against
   // 117 with 16 rows and no spill; of 1024, d = 96, 279 against 348); 16 give twice the
   // workgroups where 32 would leave CUs idle (fewer than two workgroups for each of the
-  // 256), and where 32 rows and the sort scratch would not fit the 160 KB of LDS
+  // 256), and where 32 rows and the sort scratch would not fit the 160 KB of LDS, or would leave
+  // one workgroup of eight waves a CU (96 heads of 512, k = 200, with the cache outputs, d = 64 241
+  // us, where k = 128 takes 115)
   bool tr16 = BH * ((a.Lq + 31) / 32) < 512;
-  if (a.Lk > 512 && a.scratch > 128) tr16 = true;
+  if (a.Lk > 256 && a.scratch > 128) tr16 = true;
   a.tiles_per_head = tr16 ? (a.Lq + 15) / 16 : (a.Lq + 31) / 32;
   if (a.Lk <= 256) return tr16 ? launch_rows_inst<T, D, 4, 16>(a, BH, st) : launch_rows_inst<T, D, 4, 32>(a, BH, st);
   if (a.Lk <= 512) return tr16 ? launch_rows_inst<T, D, 8, 16>(a, BH, st) : launch_rows_inst<T, D, 8, 32>(a, BH, st);

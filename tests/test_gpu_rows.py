@@ -22,6 +22,8 @@ CASES = [
     (16, 32, 20, 300, 96, 3, True), (16, 32, 5, 1024, 32, 200, False),
     # the 32-row kernels of d = 128 that keep some registers in scratch memory
     (16, 32, 33, 250, 128, 60, False), (16, 32, 20, 500, 128, 100, True),
+    # 16 rows a workgroup with the cache outputs (their sort scratch), 32 without
+    (16, 32, 40, 400, 64, 200, True),
 ]
 
 
