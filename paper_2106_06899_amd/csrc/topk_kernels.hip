@@ -101,15 +101,13 @@ __global__ __launch_bounds__(256, 3) void k_tile_scores_f32(Problem pb, Pass ps,
   constexpr int TQ = 128, TK = 64;
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, n = lane & 15,
             g = lane >> 4;
-  const int64_t NG = gridDim.x, bid = blockIdx.x;
+  const int64_t nq = (pb.C + TQ - 1) / TQ, nk = (pb.Lk + TK - 1) / TK;
   // contiguous ranges per XCD; causal heads only whole, eight at a time: a head in parts would give one
   // XCD the many tiles of its first keys and another the few of its last (calls of one head of 4096,
   // d = 64: 77 -> 64 us, by scalar tiles 73; of twelve of 2000, d = 128: 224, by scalar tiles 347)
   const int64_t NG = gridDim.x, bid = blockIdx.x;
   const int64_t by8 = pb.causal ? ps.nc / (8 * ps.nchunk) * 8 * ps.nchunk * nq * nk : NG / 8 * 8 == NG ? NG : 0;
   const int64_t wg = bid < by8 ? (bid % 8) * (by8 / 8) + bid / 8 : bid;
-  const int64_t wg = (NG % 8 == 0) ? (bid % 8) * (NG / 8) + bid / 8 : bid;
-  const int64_t nq = (pb.C + TQ - 1) / TQ, nk = (pb.Lk + TK - 1) / TK;
   const int64_t qt = wg % nq, kt = (wg / nq) % nk, cl = wg / (nq * nk);
   const int64_t key0 = kt * TK, r0 = qt * TQ + wave * 32;
   const int64_t id = ps.c0 + cl, bh = id / ps.nchunk, c = id - bh * ps.nchunk, i0 = pb.q0 + c * pb.C;
