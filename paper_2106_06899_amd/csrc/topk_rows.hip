@@ -514,8 +514,9 @@ hipError_t launch_rows_inst(RowsArgs a, int64_t BH, hipStream_t st) {
 template <typename T, int D>
 hipError_t launch_rows_d(RowsArgs a, int64_t BH, hipStream_t st) {
   // 32 rows per workgroup halve the reads of keys and values (also where their 128
-  // registers spill, bf16 values at d = 96 and 128: 96 heads of 512, d = 128, 104 us against
-  // 117 with 16 rows and no spill; of 1024, d = 96, 279 against 348); 16 give twice the
+  // registers spill: bf16 d = 96 6 to 20 of them, d = 128 36 to 39, fp32 d = 128 11 to 29, beside
+  // 66 to 94 scalar registers kept in vector lanes everywhere. 96 heads of 512, d = 128, 104 us
+  // against 117 with 16 rows and no spill; of 1024, d = 96, 279 against 348); 16 give twice the
   // workgroups where 32 would leave CUs idle (fewer than two workgroups for each of the
   // 256), and where 32 rows and the sort scratch would not fit the 160 KB of LDS, or would leave
   // one workgroup of eight waves a CU (96 heads of 512, k = 200, with the cache outputs, d = 64 241
