@@ -112,8 +112,20 @@ constexpr int ROWS_MAX_LK = 1024, ROWS_MAX_K = 256;
 inline bool rows_few(const Problem& pb) {
   return pb.dtype == T_BF16 && !pb.causal && pb.Lq <= 8 && pb.Lk > 256 && pb.BH * pb.Lk * pb.d * 4 > 210000000;
 }
+// And for d = 128 where the kernel's registers do not suffice (32 rows a workgroup, causal: its
+// waves above the diagonal idle too) or the matrix instructions of few 32-bit workgroups are a
+// long chain, with k <= 64: more kept keys cost the chunk tiles' select more. Measured (us, this
+// kernel / chunk tiles / before this kernel): bf16, causal: 48 heads of 1024, k 8 208 / 155 / 152, k 64
+// 203 / 186 / 180, k 200 200 / 316; of 600, k 64 111 / 102; 16 of 1024, k 64 81 / 78; 16 of 600 44 / 53; 96
+// of 512, k 8 121 / 123. fp32: one head of 1024, k 8 40 / 30, k 64 40 / 33 (36), k 200 40 / 40; 16 rows of it
+// 39 / 26 (32); two heads 40 / 37; four 41 / 55; one of 800, k 64 36 / 32; of 600 30 / 31.
+inline bool rows_tiled(const Problem& pb) {
+  if (pb.d != 128 || pb.k > 64) return false;
+  if (pb.dtype == T_BF16) return pb.causal && pb.Lk > 512 && pb.BH * ((pb.Lq + 31) / 32) >= 512;
+  return pb.Lk > 768 && pb.BH <= 2 && pb.BH * pb.Lq <= 2048;
+}
 inline bool rows_ok(const Problem& pb) {
-  return !pb.tile_only && pb.Lk <= ROWS_MAX_LK && !rows_few(pb) && pb.k <= ROWS_MAX_K &&
+  return !pb.tile_only && pb.Lk <= ROWS_MAX_LK && !rows_few(pb) && !rows_tiled(pb) && pb.k <= ROWS_MAX_K &&
          (pb.d == 32 || pb.d == 64 || pb.d == 96 || pb.d == 128);
 }
 hipError_t launch_rows(const Problem& pb, hipStream_t st);

@@ -186,3 +186,20 @@ def test_backward_takes_the_cells_where_they_were_faster():
     for N, d, u, k in [(4096, 256, 4096, 128), (512, 256, 1024, 64), (8192, 256, 8192, 256), (512, 768, 768, 32), (2048, 1024, 2048, 64),
                        (4096, 512, 4096, 128), (4096, 768, 4096, 100), (8192, 768, 8192, 200), (16384, 768, 65536, 512)]:
         assert not cells(ffn, N, d, u, k), (N, d, u, k)
+
+
+def test_short_rows_leave_to_the_chunk_tiles_where_those_were_faster():
+    """d = 128, at most 64 kept keys: causal bf16 heads of more than 512 keys that fill the chip with 32-row
+    workgroups, and one or two fp32 heads of more than 768. 256 bytes of workspace: the short-row kernel."""
+    def rows(B, H, n, m, d, k, causal, dt):
+        return tk.attn_workspace_bytes(B, H, n, m, d, k, 0, causal, dt) == 256
+
+    bf, f32 = tk.TOPK_BF16, tk.TOPK_F32
+    for a in [(1, 48, 1024, 1024, 128, 8, True, bf), (1, 16, 1024, 1024, 128, 64, True, bf), (1, 48, 600, 600, 128, 64, True, bf),
+              (1, 1, 1024, 1024, 128, 64, False, f32), (1, 2, 1024, 1024, 128, 8, True, f32), (1, 1, 16, 1024, 128, 64, False, f32)]:
+        assert not rows(*a), a
+        assert tk.attn_path(*a[:6], 0, *a[6:]) == 2
+    for a in [(1, 48, 1024, 1024, 128, 65, True, bf), (1, 48, 1024, 1024, 128, 64, False, bf), (1, 15, 1024, 1024, 128, 64, True, bf),
+              (1, 96, 512, 512, 128, 8, True, bf), (1, 48, 1024, 1024, 96, 8, True, bf), (1, 1, 1024, 1024, 128, 65, False, f32),
+              (1, 4, 1024, 1024, 128, 64, False, f32), (1, 1, 768, 768, 128, 8, False, f32), (1, 1, 1024, 1024, 64, 32, False, f32)]:
+        assert rows(*a), a
