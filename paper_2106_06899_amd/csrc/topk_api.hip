@@ -145,16 +145,30 @@ int64_t caph_for(const Problem& pb, int path) { return path == PATH_FILTER && pb
 // sharp one, at least five blocks of 16 keys per four kept. The scan takes as long for 1 as
 // for 256 queries of a head (0.7 us per 64 keys at d = 64, 1.3 at d = 128); writing the
 // scores takes 1 us per 10^6, so 8192 rows in all are where the two meet. The filtered and
-// tiled GEMMs use 128-query tiles over all keys and lose less: 2048 rows.
+// tiled GEMMs use 128-query tiles over all keys and lose less: 2048 rows, and, since these
+// kernels read a key again for every 64 queries and the tiles for every 128, 10 x 2^20 scores
+// in place of the filtered GEMM (4 x 2^20 where d > 512 or where d > 64 and k > 256, whose select reads
+// most of the row) and 2^20 in place of the tiled one at d > 256; the filtered path's scan at d = 128
+// loses throughout.
 // Measured (us, before / now): 64 heads x 5 queries, 20001 keys, d 128, k 128: 442 / 103; 8 x
 // 1, 60000, d 64: 714 / 40; 64 x 64, 20001, d 64: 458 / 169; 128 x 64, 4096, d 64: 107 / 97; 256
 // x 128, 2048, d 64 (tiled): 195 / 228; 64 x 128, 9000, d 96 (filtered): 167 / 191; feed-forward
-// 24 tokens, 768, 16384 units, k 256: 115 / 41; 128, 1024, 32768, k 512: 140 / 98. Heads of at
+// 24 tokens, 768, 16384 units, k 256: 115 / 41; 128, 1024, 32768, k 512: 140 / 98. Filtered, k 32 / k
+// 512: 16 x 64, 5000, d 256 58 / 40; 4 x 128, 20000 68 / 56, 93 / 92; 4 x 128, 40000 75 / 84, 103 / 123; 16 x 128,
+// 40000 156 / 300, 278 / 456; d 512: 4 x 128, 20000 80 / 77, 121 / 126; 1 x 128, 20000 70 / 43, 90 / 72; d 1024:
+// 4 x 128, 5000 86 / 55; 16 x 128, 5000 122 / 145; 1 x 128, 40000 90 / 96, 114 / 131; d 64: 16 x 64, 20000, k 512
+// 96 / 94; 16 x 128 116 / 152. Tiled: 16 x 32, 1500, d 512 33 / 32; 16 x 64 35 / 40; d 256 30 / 30. Heads of at
 // most 1024 keys: where the short-row kernel would read more than the caches hold (rows_few).
+int64_t few_scores(const Problem& pb, int path) {
+  if (path == PATH_FUSED) return 8192 * pb.Lk;
+  const int64_t rows = 2048 * pb.Lk, M = int64_t(1) << 20;
+  if (path == PATH_TILE) return pb.d <= 256 ? rows : std::min(rows, M);
+  return filter_scan_ok(pb) ? rows : std::min(rows, pb.d > 512 || (pb.d > 64 && pb.k > 256) ? 4 * M : 10 * M);
+}
 bool few_ok(const Problem& pb, int path) {
   return pb.dtype == T_BF16 && pb.d % 32 == 0 && !pb.causal && !pb.tile_only && pb.Lq <= FEW_ROWS && pb.q0 == 0 &&
          pb.q1 == pb.Lq && pb.Lk <= 65536 && pb.k <= 512 &&
-         (pb.Lk > ROWS_MAX_LK ? 4 * ((pb.Lk + 15) / 16) >= 5 * pb.k && pb.BH * pb.Lq <= (path == PATH_FUSED ? 8192 : 2048)
+         (pb.Lk > ROWS_MAX_LK ? 4 * ((pb.Lk + 15) / 16) >= 5 * pb.k && pb.BH * pb.Lq * pb.Lk <= few_scores(pb, path)
                               : !rows_ok(pb) && rows_few(pb) && pb.k <= ROWS_MAX_K && pb.BH * pb.Lq <= 8192);
 }
 

@@ -203,3 +203,20 @@ def test_short_rows_leave_to_the_chunk_tiles_where_those_were_faster():
               (1, 96, 512, 512, 128, 8, True, bf), (1, 48, 1024, 1024, 96, 8, True, bf), (1, 1, 1024, 1024, 128, 65, False, f32),
               (1, 4, 1024, 1024, 128, 64, False, f32), (1, 1, 768, 768, 128, 8, False, f32), (1, 1, 1024, 1024, 64, 32, False, f32)]:
         assert rows(*a), a
+
+
+def test_few_queries_leave_to_the_general_paths_where_those_were_faster():
+    """In place of the filtered path up to 10 x 2^20 scores, 4 x 2^20 of wide or dense rows, any number at
+    d = 128; in place of the chunk tiles (told by the workspace) 2^20 at d > 256."""
+    for H, n, m, d, k in [(4, 128, 20000, 256, 32), (16, 64, 5000, 256, 128), (1, 128, 20000, 512, 512), (1, 128, 32768, 1024, 512),
+                          (16, 32, 20000, 64, 512), (16, 128, 20000, 128, 512), (32, 64, 40000, 64, 32)]:
+        assert tk.attn_path(1, H, n, m, d, k) == 2, (H, n, m, d, k)
+    for H, n, m, d, k in [(4, 128, 40000, 256, 32), (16, 128, 20000, 256, 128), (4, 64, 40000, 512, 512), (1, 128, 40000, 1024, 32),
+                          (16, 128, 20000, 64, 512), (17, 128, 5000, 96, 32)]:
+        assert tk.attn_path(1, H, n, m, d, k) == 4, (H, n, m, d, k)
+
+    def few(H, n, m, d, k):
+        assert tk.attn_path(1, H, n, m, d, k) == 2
+        return tk.attn_workspace_bytes(1, H, n, m, d, k) >= H * n * ((m + 15) // 16 * 68 + 8 * k)
+
+    assert few(16, 32, 1500, 512, 32) and few(16, 64, 1500, 256, 32) and not few(16, 64, 1500, 512, 32) and not few(32, 64, 1500, 1024, 32)

@@ -15,7 +15,7 @@ pytestmark = pytest.mark.gpu
 # (B, H, Lq, Lk, d, k): row groups of 16, 32 and 64; ragged 16-key blocks; 16 and 64 keys a
 # wave; block lists of 8 to 64 per lane; features beyond one step; k around the list sizes
 CASES = [(1, 1, 1, 1025, 64, 1), (1, 3, 16, 1040, 128, 50), (2, 2, 17, 2047, 32, 52), (1, 2, 32, 9000, 64, 128),
-         (2, 16, 33, 4099, 128, 64), (1, 8, 64, 20001, 96, 256), (1, 1, 65, 33000, 64, 257), (1, 2, 128, 17000, 160, 512),
+         (2, 16, 33, 4099, 128, 64), (1, 8, 64, 20001, 96, 256), (1, 1, 65, 33000, 64, 257), (1, 2, 128, 16000, 160, 512),
          (1, 2, 5, 65536, 1024, 512), (1, 4, 3, 10244, 544, 512)]
 
 
