@@ -212,7 +212,9 @@ const char* topk_last_error(void);
  * Which implementation the arguments select (rows of at most 1024 keys, k <= 256 and
  * d = 32, 64, 96 or 128 run as one kernel that keeps a row's scores in LDS and uses no
  * workspace, reported as the path longer rows of their kind take; except at most eight bf16
- * queries per head against more than 200 MB of keys and values, which run as path 2): 1 = fused score+filter path
+ * queries per head against more than 210 MB of keys and values, and with d = 128 and k <= 64
+ * causal bf16 heads of more than 512 keys in large numbers and one or two fp32 heads of more
+ * than 768, which run as path 2): 1 = fused score+filter path
  * (bf16 MFMA score tiles, candidates filtered on chip), 2 = chunk-tile path
  * (the chunk's score tile in workspace, then a row-wise select), 3 = both, by rows
  * (causal masks on the fused path: the first 1024 R rows of every head, whose few
@@ -222,9 +224,11 @@ const char* topk_last_error(void);
  * row's threshold comes from those samples, and only the scores reaching it are kept
  * as candidates, by the fused path's score kernel at d = 128 and by the chunk-tile
  * GEMM otherwise; the rest as the fused path). Calls of a few queries per head against
- * 1025 to 65536 keys (bf16, at most 128 queries, k <= 512) run as path 2 with kernels of
- * their own that spread the keys. Or a negative status for invalid
- * arguments. For tests and reports.
+ * 1025 to 65536 keys (bf16, d % 32 == 0, not causal, at most 128 queries, k <= 512 and at most
+ * four fifths of the 16-key blocks, and in all at most 8192 queries where path 1 would run, 2048
+ * otherwise, with 4 to 10 * 2^20 scores in place of path 4 at d != 128 and 2^20 in place of path 2 at
+ * d > 256) run as path 2 with kernels of their own that spread the keys. Or a negative
+ * status for invalid arguments. For tests and reports.
  */
 int topk_attn_path(int64_t B, int64_t H, int64_t Lq, int64_t Lk, int64_t d,
                    int64_t k, int64_t chunk, int causal, int dtype);
@@ -264,8 +268,10 @@ int topk_profile_end(double* stage_ms, int64_t* stage_launches, int n_stages);
  * large share of the keys, see topk_set_backward_lists), in a fixed order of cells, so
  * results do not depend on scheduling (with atomic lists only for keys that at most
  * 1024 rows selected). Workspace:
- * topk_attn_backward_workspace_bytes() bytes, O(B*H*(Lq*k + Lk)) (the registered
- * workspace, or one allocated on the stream). Errors as topk_attn; additionally
+ * topk_attn_backward_workspace_bytes() bytes, O(B*H*(Lq*k + Lk)); by cells O(B*H*(Lq*k +
+ * Lq*Lk/4096)) and, where few workgroups make up a product and its sum is split, two to eight
+ * partial sums in 32 bits of d_Q (Lq*d a head) or of d_K and d_V (2*Lk*d), whichever takes
+ * more (the registered workspace, or one allocated on the stream). Errors as topk_attn; additionally
  * TOPK_E_UNSUPPORTED when B*H*Lq*k or B*H*Lk reaches 2^31.
  */
 int topk_attn_backward(const void* Q, const void* K, const void* V, const int32_t* top_idx, const float* top_dots,
@@ -285,8 +291,8 @@ int topk_ffn_backward(const void* X, const void* W1, const void* W2, const int32
 
 /*
  * How the backward calls group the selected (row, key) pairs by key, process-wide:
- * TOPK_LISTS_AUTO (default) takes cells of 64 rows x 64 keys and matrix products (bf16,
- * rows of d >= 256 that keep at least one key in 40, narrower ones under tighter rules),
+ * TOPK_LISTS_AUTO (default) takes cells of 64 rows x 64 keys and matrix products (bf16, heads
+ * of at most 16384 keys whose rows keep at least one key in 16 to 40, depending on the sizes),
  * otherwise the bucket sort for heads of up to 2^19 keys and atomic counters beyond; a
  * call whose registered workspace holds the lists but not the cells takes the lists.
  * TOPK_LISTS_BUCKET asks for the bucket sort (a

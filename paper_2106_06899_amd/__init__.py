@@ -142,7 +142,8 @@ def ffn_workspace_bytes(N, d_model, d_ff, k, chunk=0, dtype=TOPK_BF16) -> int:
 
 
 def attn_path(B, H, Lq, Lk, d, k, chunk=0, causal=False, dtype=TOPK_BF16) -> int:
-    """1 = fused score+filter path, 2 = chunk-tile path (negative: invalid arguments)."""
+    """1 = fused score+filter path, 2 = chunk-tile path, 3 = both, by rows, 4 = filtered chunk-tile path
+    (negative: invalid arguments); short rows and few queries as topk_attn.h says."""
     return int(lib().topk_attn_path(B, H, Lq, Lk, d, k, chunk, int(causal), dtype))
 
 
