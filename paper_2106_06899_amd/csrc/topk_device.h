@@ -144,11 +144,11 @@ __device__ __forceinline__ uint32_t wave_incl_scan_full(uint32_t x) {
   return x;
 }
 
-// Bitonic sort, descending, of 64*E keys held as r[e] = element (e*64 + lane).
-template <int E>
+// Bitonic sort, descending, of 64*E keys held as r[e] = element (e*64 + lane); of the first P (a
+// power of two) alone where the rest are not needed.
+template <int E, int P = 64 * E>
 __device__ __forceinline__ void wave_sort_desc(uint64_t (&r)[E]) {
   const int lane = threadIdx.x & 63;
-  constexpr int P = 64 * E;
   // fully unrolled: every shuffle distance is a compile-time constant
 #pragma unroll
   for (int size = 2; size <= P; size <<= 1) {

@@ -80,15 +80,15 @@ __device__ __forceinline__ float rows_wave_sum(float x) {
 }
 __device__ __forceinline__ float uniform(float x) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x))); }
 
-// Writes a row's n <= 64 * E distinct selected keys (in scratch, a wave's own LDS) in
-// descending order as indices and raw scores, padded to k with -1 and -inf.
-template <int E>
+// Writes a row's n <= P distinct selected keys (in scratch, a wave's own LDS) in
+// descending order as indices and raw scores, padded to k <= P with -1 and -inf.
+template <int E, int P = 64 * E>
 __device__ __forceinline__ void rows_sorted_out(const uint64_t* scratch, int n, int k, int32_t* idx, float* sc) {
   const int lane = threadIdx.x & 63;
   uint64_t r[E];
 #pragma unroll
   for (int e = 0; e < E; ++e) r[e] = e * 64 + lane < n ? scratch[e * 64 + lane] : 0ull;
-  wave_sort_desc<E>(r);
+  wave_sort_desc<E, P>(r);
 #pragma unroll
   for (int e = 0; e < E; ++e) {
     const int t = e * 64 + lane;
@@ -316,7 +316,10 @@ __global__ __launch_bounds__(64 * E, 4) void k_rows(RowsArgs a) {
         const int64_t o = (bh * a.Lq + i) * a.k;
         int32_t* ip = a.idx_out ? a.idx_out + o : nullptr;
         float* sp = a.score_out ? a.score_out + o : nullptr;
-        if (a.k <= 64) rows_sorted_out<1>(sc, k_eff, a.k, ip, sp);
+        // (6, 15 or 21 steps of the network: 48 causal heads of 1024, d = 64, k 8 162 -> 148 us)
+        if (a.k <= 8) rows_sorted_out<1, 8>(sc, k_eff, a.k, ip, sp);
+        else if (a.k <= 32) rows_sorted_out<1, 32>(sc, k_eff, a.k, ip, sp);
+        else if (a.k <= 64) rows_sorted_out<1>(sc, k_eff, a.k, ip, sp);
         else if (a.k <= 128) rows_sorted_out<2>(sc, k_eff, a.k, ip, sp);
         else rows_sorted_out<4>(sc, k_eff, a.k, ip, sp);
         wave_sync_lds();

@@ -24,6 +24,8 @@ CASES = [
     (16, 32, 33, 250, 128, 60, False), (16, 32, 20, 500, 128, 100, True),
     # 16 rows a workgroup with the cache outputs (their sort scratch), 32 without
     (16, 32, 40, 400, 64, 200, True),
+    # as many kept keys as the sorts of the cache outputs hold, and one more
+    (1, 2, 50, 300, 64, 8, True), (1, 2, 50, 300, 64, 9, False), (1, 2, 50, 600, 32, 32, True), (1, 2, 50, 200, 64, 33, True),
 ]
 
 
