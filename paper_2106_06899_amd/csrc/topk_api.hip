@@ -218,6 +218,9 @@ void choose_path(const Problem& pb, Plan* pl) {
 void choose_path_for(Problem* pb, Plan* pl) {
   choose_path(*pb, pl);
   if (pl->few_whole) pb->C = pb->Lq;
+  // short rows as chunk tiles: the tiles of no more rows at a time than the default, which the
+  // fixed scratch holds, whatever the caller's chunk
+  if (rows_can(*pb) && pb->C > DEFAULT_CHUNK) pb->C = DEFAULT_CHUNK;
 }
 
 size_t row_bytes(const Problem& pb, const Plan& pl) {
@@ -361,6 +364,7 @@ int run(Problem whole, hipStream_t st, bool report, void* fixed_ws = nullptr, si
     }
     need = n > need ? n : need;
   }
+  if (ws_given && need > ws_given_bytes && rows_can(whole)) return run_rows(whole, st, report);  // needs no workspace
   char* ws = (char*)ws_given;
   bool own = false;
   if (fixed_ws) {
@@ -372,8 +376,11 @@ int run(Problem whole, hipStream_t st, bool report, void* fixed_ws = nullptr, si
       return fail(TOPK_E_NOMEM, "registered workspace of %zu bytes is below the %zu bytes one query chunk needs",
                   g_ws_bytes, need);
   } else {
-    if (hipMallocAsync((void**)&ws, need, st) != hipSuccess)
+    if (hipMallocAsync((void**)&ws, need, st) != hipSuccess) {
+      (void)hipGetLastError();
+      if (rows_can(whole)) return run_rows(whole, st, report);
       return fail(TOPK_E_NOMEM, "could not allocate %zu bytes of workspace", need);
+    }
     own = true;
   }
   hipError_t e = hipSuccess;

@@ -124,10 +124,12 @@ inline bool rows_tiled(const Problem& pb) {
   if (pb.dtype == T_BF16) return pb.causal && pb.Lk > 512 && pb.BH * ((pb.Lq + 31) / 32) >= 512;
   return pb.Lk > 768 && pb.BH <= 2 && pb.BH * pb.Lq <= 2048;
 }
-inline bool rows_ok(const Problem& pb) {
-  return !pb.tile_only && pb.Lk <= ROWS_MAX_LK && !rows_few(pb) && !rows_tiled(pb) && pb.k <= ROWS_MAX_K &&
+// the calls the kernel can run, and those it does (the others where a given workspace is too small)
+inline bool rows_can(const Problem& pb) {
+  return !pb.tile_only && pb.Lk <= ROWS_MAX_LK && pb.k <= ROWS_MAX_K &&
          (pb.d == 32 || pb.d == 64 || pb.d == 96 || pb.d == 128);
 }
+inline bool rows_ok(const Problem& pb) { return rows_can(pb) && !rows_few(pb) && !rows_tiled(pb); }
 hipError_t launch_rows(const Problem& pb, hipStream_t st);
 
 // Few queries (k_few_scores, k_few_select): their score rows are padded to whole blocks of 16.

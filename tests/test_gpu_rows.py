@@ -139,3 +139,46 @@ def test_short_rows_beyond_one_launch():
     for b in range(0, B, 512):
         v[b:b + 512] = torch.randn(512, H, 1, 32, generator=gen, device="cuda")
     assert torch.equal(tk.attn(q, q, v, 1), v)
+
+
+# calls of short rows that run as chunk tiles or with the few-query kernels
+LEFT = [(1, 1, 300, 1024, 128, 8, False, torch.float32), (1, 16, 1030, 600, 128, 20, True, torch.bfloat16),
+        (1, 900, 2, 1000, 64, 40, False, torch.bfloat16)]
+
+
+@pytest.mark.parametrize("case", LEFT)
+def test_short_rows_in_a_workspace_too_small_for_the_general_paths(case):
+    """The short-row kernel, which needs none, runs them there."""
+    B, H, Lq, Lk, d, k, causal, dtype = case
+    print("[case]", case, flush=True)
+    dt = tk.TOPK_BF16 if dtype == torch.bfloat16 else tk.TOPK_F32
+    assert tk.attn_workspace_bytes(B, H, Lq, Lk, d, k, 0, causal, dt) > 256
+    gen = torch.Generator(device="cuda").manual_seed(11)
+    q, kk, v = (torch.randn(B, H, n, d, generator=gen, device="cuda").to(dtype) for n in (Lq, Lk, Lk))
+    ref, got = tk.attn(q, kk, v, k, 0, causal, 0.1), torch.empty_like(q)
+    ws = torch.empty(4096, dtype=torch.uint8, device="cuda")
+    tk._raise(tk.lib().topk_set_workspace(ws.data_ptr(), 4096))
+    try:
+        tk._raise(tk.lib().topk_attn(q.data_ptr(), kk.data_ptr(), v.data_ptr(), got.data_ptr(), B, H, Lq, Lk, d, k, 0, int(causal), 0.1, dt,
+                                     torch.cuda.current_stream().cuda_stream))
+        torch.cuda.synchronize()
+    finally:
+        tk.lib().topk_set_workspace(None, 0)
+    # sums in another order; in bf16 a result on the other side of a rounding (2^-8)
+    tol = 2.0 ** -7 if dtype == torch.bfloat16 else 1e-5
+    assert bool(((got.float() - ref.float()).abs().amax(-1) <= tol * ref.float().abs().amax(-1)).all())
+
+
+def test_short_rows_as_chunk_tiles_in_the_fixed_scratch():
+    """Whatever the chunk: the tiles of at most 1024 rows at a time."""
+    gen = torch.Generator(device="cuda").manual_seed(12)
+    q = torch.randn(1, 1, 70000, 128, generator=gen, device="cuda").bfloat16()
+    kk, v = (torch.randn(1, 1, 1000, 128, generator=gen, device="cuda").bfloat16() for _ in range(2))
+    assert tk.attn_workspace_bytes(1, 1, 70000, 1000, 128, 8, 70000, True) > 256
+    ref = tk.attn(q, kk, v, 8, 512, True, 0.1)
+    assert torch.equal(tk.attn(q, kk, v, 8, 70000, True, 0.1), ref)
+    got = torch.empty_like(q)
+    tk._raise(tk.lib().topk_attn_noalloc(q.data_ptr(), kk.data_ptr(), v.data_ptr(), got.data_ptr(), 1, 1, 70000, 1000, 128, 8, 70000, 1, 0.1,
+                                         tk.TOPK_BF16, torch.cuda.current_stream().cuda_stream))
+    torch.cuda.synchronize()
+    assert torch.equal(got, ref)
