@@ -160,16 +160,21 @@ int64_t caph_for(const Problem& pb, int path) { return path == PATH_FILTER && pb
 // 96 / 94; 16 x 128 116 / 152. Tiled: 16 x 32, 1500, d 512 33 / 32; 16 x 64 35 / 40; d 256 30 / 30. Heads of at
 // most 1024 keys: where the short-row kernel would read more than the caches hold (rows_few).
 int64_t few_scores(const Problem& pb, int path) {
-  if (path == PATH_FUSED) return 8192 * pb.Lk;
-  const int64_t rows = 2048 * pb.Lk, M = int64_t(1) << 20;
-  if (path == PATH_TILE) return pb.d <= 256 ? rows : std::min(rows, M);
-  return filter_scan_ok(pb) ? rows : std::min(rows, pb.d > 512 || (pb.d > 64 && pb.k > 256) ? 4 * M : 10 * M);
+  const int64_t M = int64_t(1) << 20;
+  if (path == PATH_FUSED || (path == PATH_FILTER && filter_scan_ok(pb))) return INT64_MAX;
+  if (path == PATH_TILE) return pb.d <= 256 ? INT64_MAX : M;
+  return pb.d > 512 || (pb.d > 64 && pb.k > 256) ? 4 * M : 10 * M;
 }
-bool few_ok(const Problem& pb, int path) {
+// the calls that can take these kernels, and those that do (the others where a given workspace holds
+// their scores, but not the fallback rows of the path that is faster)
+bool few_can(const Problem& pb, int path) {
   return pb.dtype == T_BF16 && pb.d % 32 == 0 && !pb.causal && !pb.tile_only && pb.Lq <= FEW_ROWS && pb.q0 == 0 &&
          pb.q1 == pb.Lq && pb.Lk <= 65536 && pb.k <= 512 &&
-         (pb.Lk > ROWS_MAX_LK ? 4 * ((pb.Lk + 15) / 16) >= 5 * pb.k && pb.BH * pb.Lq * pb.Lk <= few_scores(pb, path)
+         (pb.Lk > ROWS_MAX_LK ? 4 * ((pb.Lk + 15) / 16) >= 5 * pb.k && pb.BH * pb.Lq <= (path == PATH_FUSED ? 8192 : 2048)
                               : !rows_ok(pb) && rows_few(pb) && pb.k <= ROWS_MAX_K && pb.BH * pb.Lq <= 8192);
+}
+bool few_ok(const Problem& pb, int path) {
+  return few_can(pb, path) && (pb.Lk <= ROWS_MAX_LK || pb.BH * pb.Lq * pb.Lk <= few_scores(pb, path));
 }
 
 void choose_long_path(const Problem& pb, Plan* pl) {
@@ -208,15 +213,15 @@ void choose_long_path(const Problem& pb, Plan* pl) {
   }
 }
 
-void choose_path(const Problem& pb, Plan* pl) {
+void choose_path(const Problem& pb, Plan* pl, bool few_wanted = false) {
   choose_long_path(pb, pl);
-  pl->few = few_ok(pb, pl->path);
+  pl->few = few_wanted ? few_can(pb, pl->path) : few_ok(pb, pl->path);
   pl->few_whole = pl->few && pl->path != PATH_TILE;
   if (pl->few) pl->path = PATH_TILE;
 }
 // the path, and the problem as that path runs it
-void choose_path_for(Problem* pb, Plan* pl) {
-  choose_path(*pb, pl);
+void choose_path_for(Problem* pb, Plan* pl, bool few_wanted = false) {
+  choose_path(*pb, pl, few_wanted);
   if (pl->few_whole) pb->C = pb->Lq;
   // short rows as chunk tiles: the tiles of no more rows at a time than the default, which the
   // fixed scratch holds, whatever the caller's chunk
@@ -359,6 +364,10 @@ int run(Problem whole, hipStream_t st, bool report, void* fixed_ws = nullptr, si
     if (ws_given && n > ws_given_bytes && plans[q].few && !plans[q].few_whole) {
       // a workspace that holds a chunk's scores, but not their block maxima as well
       plans[q].few = false;
+      plan_sizes(parts[q], &plans[q], budget);
+      n = plan_total(plans[q], parts[q]);
+    } else if (ws_given && n > ws_given_bytes && plans[q].path == PATH_FILTER && few_can(parts[q], PATH_FILTER)) {
+      choose_path_for(&parts[q], &plans[q], true);
       plan_sizes(parts[q], &plans[q], budget);
       n = plan_total(plans[q], parts[q]);
     }

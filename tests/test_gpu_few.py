@@ -156,3 +156,18 @@ def test_few_queries_against_many_short_rows(case):
         assert bool(((out[:, h:h + 64].double() - ref).abs() <= 2.0 ** -8 * ref.abs() + 1e-5).all())
     for C in (1, 3):
         assert torch.equal(tk.attn(q, kk, v, k, C), out)
+
+
+def test_few_queries_where_the_filtered_path_does_not_fit():
+    """More scores than these kernels are the faster for, in the fixed scratch, which the filtered
+    path's fallback rows exceed: they run there."""
+    H, Lq, Lk, d, k = 1, 100, 45000, 256, 512
+    assert tk.attn_path(1, H, Lq, Lk, d, k) == 4 and tk.attn_workspace_bytes(1, H, Lq, Lk, d, k) > tk.lib().topk_noalloc_scratch_bytes()
+    gen = torch.Generator(device="cuda").manual_seed(8)
+    q, kk, v = (torch.randn(1, H, n, d, generator=gen, device="cuda").bfloat16() for n in (Lq, Lk, Lk))
+    ref, got = tk.attn(q, kk, v, k), torch.empty_like(q)
+    tk._raise(tk.lib().topk_attn_noalloc(q.data_ptr(), kk.data_ptr(), v.data_ptr(), got.data_ptr(), 1, H, Lq, Lk, d, k, 0, 0, d ** -0.5,
+                                         tk.TOPK_BF16, torch.cuda.current_stream().cuda_stream))
+    torch.cuda.synchronize()
+    # sums in another order: a result on the other side of a rounding (2^-8)
+    assert bool(((got.float() - ref.float()).abs().amax(-1) <= 2.0 ** -7 * ref.float().abs().amax(-1)).all())
