@@ -260,7 +260,11 @@ hipError_t launch_backward_cells(const BwdProblem& bp, const CellBufs& cb, hipSt
 //   534 / 474; one in 12: 16 of 2048 471 / 333, c 465 / 431; one in 32: 16 of 4096 726 / 902; k 512: 2 of
 //   8192 779 / 667, c 1063 / 910. d = 160: 16 of 1024, 64 205 / 150, c 207 / 178.
 //  d = 256: 16 heads of 1024, k 64 203 / 160, c 208 / 188; 8 of them 129 / 125, c 135 / 145; one key in
-//   24: 8 of 2048 249 / 246, c 247 / 283; k 256: 1 head of 4096 221 / 200, c 340 / 295.
+//   24: 8 of 2048 249 / 246, c 247 / 283; 24 664 / 617, c 666 / 571; k 256: 1 head of 4096 221 / 200, c 340
+//   / 295; one in 32: heads of 512: 16 78 / 87, 32 117 / 106, c 120 / 106; 32 of 1024 233 / 209, c 237 / 223; 64
+//   of 100, k 4 68 / 50; of
+//   2048: 24 504 / 573, 64 1371 / 1330, c 1392 / 1122. d = 768, one in 32: 16 of 512 125 / 128, 32 212 / 171; 32
+//   of 1024 605 / 504; 24 of 2048 1743 / 1403, c 1605 / 1113; 512 heads of one row and 1000 keys 787 / 1023.
 //  Feed-forward d = 256: 4096 tokens and units: k 256 221 / 189, 170 161 / 170; 512 tokens, 1024, 64 60
 //   / 73; 8192, 1024, 64 187 / 146; 8192, 4096, 170 280 / 274; 8192, 8192, 256 422 / 478; 8192, 16384, 512
 //   922 / 802.
@@ -269,22 +273,33 @@ hipError_t launch_backward_cells(const BwdProblem& bp, const CellBufs& cb, hipSt
 //   16384 of these 800 / 768; 128 of these 131 / 87; 4096, 768, 4096, 128 355 / 339, k 100 295 / 335; 2048, 1024,
 //   8192, 256 468 / 394; 2048, 768, 16384, 410 688 / 580; 8192, 768, 8192, 200 1103 / 1177; 16384 of these
 //   2365 / 2270; 16384, 768, 4096, 512 5263 / 1445; 64, 1024, 2048, 64 86 / 76; 1, 768, 4096, 512 402 / 79.
-inline bool cells_ok(const BwdProblem& bp) {
+// cells_can: the calls that can run by cells (also where a given workspace does not hold the lists).
+inline bool cells_can(const BwdProblem& bp) {
   if (bp.list_mode != 0 || bp.dtype != T_BF16 || bp.d % 32 != 0 || bp.Lk > (int64_t)64 * CELL_MAX) return false;
   // every launch below 2^32 threads: 1024 a strip; 256 a tile of the products, whose column
   // tiles (at most four) and two sides make eight at most
   const int64_t tq = (bp.Lq + 127) / 128, tk = (bp.Lk + 127) / 128;
   if (bp.BH * ((bp.Lq + 63) / 64) >= 1 << 22 || bp.BH * (tq > tk ? tq : tk) * 8 >= 1 << 24 || bp.BH * tq * tk >= 1 << 24) return false;
-  const int64_t d = bp.d, k = bp.k, Lk = bp.Lk, tiles = bp.BH * tq;
+  return bp.d == 64 || bp.d >= 128;
+}
+inline bool cells_ok(const BwdProblem& bp) {
+  if (!cells_can(bp)) return false;
+  const int64_t d = bp.d, k = bp.k, Lk = bp.Lk, tiles = bp.BH * ((bp.Lq + 127) / 128);
   if (d == 64) return Lk <= 16 * k && Lk <= 1024 && tiles >= (Lk <= 768 ? 256 : 384);
-  if (d < 128) return false;
-  if (bp.act == ACT_SOFTMAX || d < 256) {
+  if (d < 256) {
     if (Lk > 16 * k) return false;
-    if (k >= (d >= 256 ? 256 : 512) && tiles >= (d >= 256 ? 16 : 64)) return true;
-    return tiles >= (d > 128 || Lk <= 512 ? 128 : Lk <= 1024 || Lk <= 12 * k ? 256 : 384);
+    return (k >= 512 && tiles >= 64) || tiles >= (d > 128 || Lk <= 512 ? 128 : Lk <= 1024 || Lk <= 12 * k ? 256 : 384);
+  }
+  int64_t most = 0;  // keys or units per kept one
+  if (bp.act == ACT_SOFTMAX) {
+    if (d >= 512 && Lk > 512 && bp.Lq < 64 && k < 128) return false;
+    if (tiles >= 128 || (k >= 256 && tiles >= 16)) most = 16;
+    if (tiles >= 384) most = 25;
+    if (tiles >= 64 && Lk <= 320) most = 32;
+    if (tiles >= (Lk <= 512 ? 128 : Lk <= 1024 ? 256 : d >= 512 ? 384 : 1024)) most = Lk <= 512 ? 40 : 34;
+    return Lk <= most * k;
   }
   const int64_t N = bp.Lq;
-  int64_t most = 0;  // units per kept unit
   if (d >= 512) {
     if (k >= 64 || N >= 2048) most = 16;
     if (k >= 128 || N >= 8192) most = 25;

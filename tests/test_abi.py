@@ -175,10 +175,12 @@ def test_backward_takes_the_cells_where_they_were_faster():
 
     attn, ffn = L.topk_attn_backward_workspace_bytes, L.topk_ffn_backward_workspace_bytes
     for B, H, n, d, k in [(4, 12, 1024, 64, 64), (1, 64, 512, 64, 32), (1, 32, 1024, 128, 64), (1, 24, 2048, 128, 128), (1, 16, 2048, 128, 171),
-                          (1, 2, 8192, 128, 512), (1, 16, 1024, 160, 64), (1, 16, 1024, 256, 64), (1, 1, 4096, 256, 256)]:
+                          (1, 2, 8192, 128, 512), (1, 16, 1024, 160, 64), (1, 16, 1024, 256, 64), (1, 1, 4096, 256, 256),
+                          (1, 32, 512, 256, 13), (1, 32, 1024, 256, 32), (1, 24, 2048, 768, 64), (1, 24, 2048, 256, 86)]:
         assert cells(attn, B, H, n, n, d, k), (H, n, d, k)
     for B, H, n, d, k in [(1, 32, 1024, 64, 64), (1, 40, 1000, 64, 63), (1, 48, 1100, 64, 128), (1, 16, 2048, 128, 128), (1, 16, 1024, 128, 64),
-                          (1, 16, 4096, 128, 128), (1, 8, 2048, 128, 256), (1, 16, 1024, 96, 64), (1, 8, 1024, 256, 64), (1, 8, 2048, 256, 86)]:
+                          (1, 16, 4096, 128, 128), (1, 8, 2048, 128, 256), (1, 16, 1024, 96, 64), (1, 8, 1024, 256, 64), (1, 8, 2048, 256, 86),
+                          (1, 16, 512, 256, 16), (1, 24, 2048, 256, 64), (1, 16, 512, 768, 16)]:
         assert not cells(attn, B, H, n, n, d, k), (H, n, d, k)
     for N, d, u, k in [(16384, 768, 4096, 512), (16384, 768, 16384, 512), (4096, 256, 4096, 256), (8192, 256, 16384, 512), (512, 512, 1024, 64),
                        (2048, 768, 300, 20), (4096, 768, 4096, 128), (1, 768, 4096, 512), (2048, 768, 16384, 410)]:
