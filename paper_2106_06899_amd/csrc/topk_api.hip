@@ -669,9 +669,13 @@ size_t cell_bytes(const BwdProblem& bp) {
 int run_backward(const BwdProblem& bp, hipStream_t st) {
   bool cells = cells_ok(bp);
   size_t need = cells ? cell_bytes(bp) : bwd_bytes(bp);
-  if (cells && g_ws && need > g_ws_bytes) {  // a workspace too small for the cells may do for the lists
+  // a workspace too small for the cells may do for the lists, and the other way round
+  if (g_ws && need > g_ws_bytes && cells) {
     cells = false;
     need = bwd_bytes(bp);
+  } else if (g_ws && need > g_ws_bytes && cells_can(bp) && cell_bytes(bp) <= g_ws_bytes) {
+    cells = true;
+    need = cell_bytes(bp);
   }
   char* ws = (char*)g_ws;
   bool own = false;

@@ -186,6 +186,32 @@ def test_cells_need_more_workspace_than_lists():
         assert torch.equal(p, r)
 
 
+def test_cells_where_the_lists_do_not_fit():
+    """A registered workspace that holds the cells of a call that the lists finish sooner, but not the
+    lists: many pairs in unsplit products."""
+    L = tk.lib()
+    B, H, n, d, k = 1, 24, 2048, 64, 512
+    assert not _attn_by_cells(B, H, n, n, d, k)
+    lists = L.topk_attn_backward_workspace_bytes(B, H, n, n, d, k, tk.TOPK_BF16)
+    gen = torch.Generator(device="cuda").manual_seed(13)
+    q, kk, v, g = (torch.randn(B, H, n, d, generator=gen, device="cuda").bfloat16() for _ in range(4))
+    _, idx, dots = tk.attn(q, kk, v, k, cache=True)
+    want = tk.attn_backward(q, kk, v, idx, dots, g)
+    out = [torch.empty_like(q) for _ in range(3)]
+    size = lists * 3 // 4 // 256 * 256
+    ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+    tk._raise(L.topk_set_workspace(ctypes.c_void_p(ws.data_ptr()), size))
+    try:
+        tk._raise(L.topk_attn_backward(q.data_ptr(), kk.data_ptr(), v.data_ptr(), idx.data_ptr(), dots.data_ptr(), g.data_ptr(), out[0].data_ptr(),
+                                       out[1].data_ptr(), out[2].data_ptr(), B, H, n, n, d, k, d ** -0.5, tk.TOPK_BF16,
+                                       ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)))
+    finally:
+        L.topk_set_workspace(None, 0)
+    torch.cuda.synchronize()
+    for p, r in zip(out, want):
+        _close(p, r)
+
+
 @pytest.mark.parametrize("dm", [256, 288, 1024])
 def test_cells_keep_32_bits(dm):
     """Weights and score gradients of 18 significant bits that cancel to their last bits: exact in 32
