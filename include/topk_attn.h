@@ -294,7 +294,7 @@ int topk_ffn_backward(const void* X, const void* W1, const void* W2, const int32
  * TOPK_LISTS_AUTO (default) takes cells of 64 rows x 64 keys and matrix products (bf16, heads
  * of at most 16384 keys whose rows keep at least one key in 16 to 40, depending on the sizes),
  * otherwise the bucket sort for heads of up to 2^19 keys and atomic counters beyond; a
- * call whose registered workspace holds the lists but not the cells takes the lists.
+ * call whose registered workspace holds only one of the two takes that one.
  * TOPK_LISTS_BUCKET asks for the bucket sort (a
  * backward call on a larger head then fails with TOPK_E_UNSUPPORTED);
  * TOPK_LISTS_ATOMIC asks for the atomic counters. The bucket sort (a two-level
